@@ -2,8 +2,10 @@
 // cache, with an optional split of the KV range into chunks (merged by
 // k_decode_combine).
 //
-// One wave owns one (sequence b, KV head kh, chunk s) and all G query heads
-// of kh (padded to GP = 1, 2, 4, 8 or 16 rows).  Per 64-token group:
+// One wave, or a work-group of W = 2, 4 or 8 waves with a group each (further
+// below, the same results bit for bit), owns one (sequence b, KV head kh, chunk
+// s) and all G query heads of kh (padded to GP = 1, 2, 4, 8 or 16 rows).  Per
+// 64-token group:
 //
 //  * QK^T on the raw codes.  With w_c = q_c * s_c split exactly as
 //    w = 128*hi + lo (lo in 0..127, hi in -75..74, both int8), the int32
@@ -250,39 +252,13 @@ struct GroupV {
   unsigned vs4, vz4;           // V scales / zeros of channels 2L&~3 .. +3 (aligned dwords)
 };
 
+// The K codes of a group, and the K scales and zeros the lane needs.
 template <int BITS>
-__device__ __forceinline__ void load_k(const DecodeArgs& a, int kh, int head_off, const int* bt,
-                                       const int* gt, int g, bool live, GroupK<BITS>& K) {
+__device__ __forceinline__ void load_codes(const DecodeArgs& a, int kh, int head_off,
+                                           GroupK<BITS>& K) {
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g4 = lane >> 4, m = lane & 15;
-  g = live ? g : 0;
-  bool ok = live;
-  // the tables are read-only here: read them through the constant address
-  // space, which keeps these wave-uniform reads on the scalar unit
-  typedef const __attribute__((address_space(4))) int cint;
-  const cint* btc = (const cint*)bt;
-  const cint* gtc = (const cint*)gt;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int p = btc[4 * g + i];
-    ok = ok && p >= 0 && p < a.npages32;
-    K.pg[i] = p;
-  }
-  const int slot = gtc[g];
-  ok = ok && slot >= 0 && slot < a.nslots32;
-  K.ok = ok;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) K.pg[i] = ok ? K.pg[i] : 0;
-  K.slot = ok ? slot : 0;
-  // this lane's V page, read by the lane itself (no per-lane choice among
-  // the four uniform values)
-  const int vp = bt[4 * g + g4];
-  K.vpg = ok ? vp : 0;
   const int8_t* meta = a.gmeta + ((long)K.slot * a.Hkv + kh) * 512;
-  typedef const __attribute__((address_space(4))) float cfloat;
-  const cfloat* gs = (const cfloat*)(a.gscale + ((long)K.slot * a.Hkv + kh) * 2);
-  K.skg = gs[0];
-  K.svg = gs[1];
   const int koff = head_off + m * 16 * BITS + 4 * BITS * g4;
   // the codes are read once per launch: streaming loads.  The group's
   // metadata stays on ordinary loads, since its block is read twice (the K
@@ -312,6 +288,91 @@ __device__ __forceinline__ void load_k(const DecodeArgs& a, int kh, int head_off
   }
 }
 
+// Group g, its table entries and scales read here (scalar loads).
+template <int BITS>
+__device__ __forceinline__ void load_k(const DecodeArgs& a, int kh, int head_off, const int* bt,
+                                       const int* gt, int g, bool live, GroupK<BITS>& K) {
+  g = live ? g : 0;
+  bool ok = live;
+  // the tables are read-only here: read them through the constant address
+  // space, which keeps these wave-uniform reads on the scalar unit
+  typedef const __attribute__((address_space(4))) int cint;
+  const cint* btc = (const cint*)bt;
+  const cint* gtc = (const cint*)gt;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int p = btc[4 * g + i];
+    ok = ok && p >= 0 && p < a.npages32;
+    K.pg[i] = p;
+  }
+  const int slot = gtc[g];
+  ok = ok && slot >= 0 && slot < a.nslots32;
+  K.ok = ok;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) K.pg[i] = ok ? K.pg[i] : 0;
+  K.slot = ok ? slot : 0;
+  // this lane's V page, read by the lane itself (no per-lane choice among
+  // the four uniform values)
+  const int vp = bt[4 * g + ((threadIdx.x & 63) >> 4)];
+  K.vpg = ok ? vp : 0;
+  typedef const __attribute__((address_space(4))) float cfloat;
+  const cfloat* gs = (const cfloat*)(a.gscale + ((long)K.slot * a.Hkv + kh) * 2);
+  K.skg = gs[0];
+  K.svg = gs[1];
+  load_codes<BITS>(a, kh, head_off, K);
+}
+
+// Table entries and float scales of the wave's next 64 groups, lane i holding
+// those of its i-th one: read once per 64 steps with vector loads, so that no
+// step waits for a table entry before its code loads can leave, nor for a
+// scalar load at its next LDS access (the two share a wait counter).
+struct GroupTab {
+  int pg[4];      // page of each 16-token quarter, 0 if the group is not live
+  int slot;       // group slot, -1 if the group is not live or out of range
+  float sk, sv;   // float scales of the group
+};
+
+// Lane i: group g + i * W of the sequence whose tables are bt, gt (live below g1).
+template <int W>
+__device__ __forceinline__ void load_tab(const DecodeArgs& a, int kh, const int* bt, const int* gt,
+                                         int g, int g1, GroupTab& T) {
+  g += (int)(threadIdx.x & 63) * W;
+  const bool live = g < g1;
+  g = live ? g : 0;
+  bool ok = live;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    T.pg[i] = bt[4 * g + i];
+    ok = ok && T.pg[i] >= 0 && T.pg[i] < a.npages32;
+  }
+  const int slot = gt[g];
+  ok = ok && slot >= 0 && slot < a.nslots32;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) T.pg[i] = ok ? T.pg[i] : 0;
+  T.slot = ok ? slot : -1;
+  const float* gs = a.gscale + ((long)max(T.slot, 0) * a.Hkv + kh) * 2;
+  T.sk = gs[0];
+  T.sv = gs[1];
+}
+
+// The i-th group of T (i wave-uniform).
+template <int BITS>
+__device__ __forceinline__ void load_k(const DecodeArgs& a, int kh, int head_off, const GroupTab& T,
+                                       int i, GroupK<BITS>& K) {
+  const int g4 = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) K.pg[q] = __builtin_amdgcn_readlane(T.pg[q], i);
+  K.slot = __builtin_amdgcn_readlane(T.slot, i);
+  K.ok = K.slot >= 0;
+  K.slot = max(K.slot, 0);
+  K.skg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(T.sk), i));
+  K.svg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(T.sv), i));
+  // this lane's V page
+  const int p01 = g4 & 1 ? K.pg[1] : K.pg[0], p23 = g4 & 1 ? K.pg[3] : K.pg[2];
+  K.vpg = g4 & 2 ? p23 : p01;
+  load_codes<BITS>(a, kh, head_off, K);
+}
+
 template <int BITS>
 __device__ __forceinline__ void load_v(const DecodeArgs& a, int kh, int head_off,
                                        const GroupK<BITS>& K, GroupV<BITS>& V) {
@@ -332,12 +393,200 @@ __device__ __forceinline__ void load_v(const DecodeArgs& a, int kh, int head_off
   V.vz4 = *reinterpret_cast<const unsigned*>(meta + 384 + 4 * (lane >> 1));
 }
 
+// q -> int8 per (b, query head) (Algorithm 2; eq. step1bpq) into the wave's
+// LDS: lane (n, g4) codes channels 32*g4 .. 32*g4+31 of row n (zero if n >= G)
+template <int GP, bool kTrace>
+__device__ __forceinline__ void decode_quant_q(const DecodeArgs& a, float* sqv,
+                                               signed char (*qbuf)[128], int b, int kh, int trow) {
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, g4 = lane >> 4;
+  const bool rowok = n < a.G;
+  int q8w[8];
+  uint4 raw[4];
+  float amax = 0.0f;
+  const uint4* src = a.q + ((long)b * a.Hq + kh * a.G + (rowok ? n : 0)) * 16;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    raw[u] = rowok ? src[4 * g4 + u] : make_uint4(0, 0, 0, 0);
+    f16x8_t hv = __builtin_bit_cast(f16x8_t, raw[u]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)hv[e]));
+  }
+  amax = max_xor16(amax);
+  amax = max_xor32(amax);
+  float inv = 0.0f, sq = 0.0f;
+  if (amax > 0.0f) {
+    sq = amax / kQmax;
+    inv = kQmax / amax;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    f16x8_t hv = __builtin_bit_cast(f16x8_t, raw[u]);
+    int qv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qv[e] = rne_mul((float)hv[e], inv);
+    q8w[2 * u] = pack4(qv[0], qv[1], qv[2], qv[3]);
+    q8w[2 * u + 1] = pack4(qv[4], qv[5], qv[6], qv[7]);
+  }
+  if (g4 == 0) sqv[n] = sq;
+  if (n < kWRows<GP>) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<int*>(&qbuf[n][32 * g4 + 4 * i]) = q8w[i];
+  }
+  if (kTrace && trow >= 0 && n == trow) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) reinterpret_cast<int*>(a.trace + TURBO_TRACE_Q8)[8 * g4 + i] = q8w[i];
+    if (g4 == 0) *reinterpret_cast<float*>(a.trace + TURBO_TRACE_SQ) = sq;
+  }
+}
+
+// w = q * s^int of the GP query rows, written by all lanes of a wave.
+// The QK^T B-operand of lane (n, g4), k-step ks, is 16 bytes: dword j, byte
+// i holds channel 32*g4 + c0 + d*i with c0 = 16ks + 8(j>>1) + (j&1) (int4)
+// or 16ks + j (int2), the order the K codes unpack to.  Only GP of the 16
+// rows n are real, so instead of every lane building its own 32 values,
+// lane L builds those of unit U = L + 64t: row U >> 4, 8 channels given by
+// k = U & 15 -- dwords j = 2h, 2h+1 (h = k & 1) of block (g4 = k >> 2,
+// ks = (k >> 1) & 1) -- and writes their hi/lo bytes to byte 8k of the row.
+template <int GP, int BITS>
+struct QueryW {
+  static constexpr int kU = GP <= 4 ? 1 : GP / 4;  // writer units per lane
+  unsigned wq[kU][4];  // 16-bit q pairs (A0,A1) (A2,A3) (B0,B1) (B2,B3)
+  int wqn[kU][2];      // the q bytes of dword A (= 2h) and B (= 2h + 1)
+  unsigned selA, selZ1, selZ2;  // int2: byte selectors of channel 2h (+1) in the block's dwords
+
+  __device__ __forceinline__ void load(const signed char (*qbuf)[128]) {
+    constexpr int d = BITS == 4 ? 2 : 4;
+    const int lane = threadIdx.x & 63, k = lane & 15;
+    const int cA = BITS == 4 ? 8 * k : 16 * (k >> 1) + 2 * (k & 1);  // channel of dword 2h, byte 0
+#pragma unroll
+    for (int t = 0; t < kU; ++t) {
+      const int r = (lane >> 4) + 4 * t;
+      int qa[4], qb[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        qa[i] = qbuf[r][cA + d * i];
+        qb[i] = qbuf[r][cA + 1 + d * i];
+      }
+      wq[t][0] = ((unsigned)qa[0] & 0xffffu) | ((unsigned)qa[1] << 16);
+      wq[t][1] = ((unsigned)qa[2] & 0xffffu) | ((unsigned)qa[3] << 16);
+      wq[t][2] = ((unsigned)qb[0] & 0xffffu) | ((unsigned)qb[1] << 16);
+      wq[t][3] = ((unsigned)qb[2] & 0xffffu) | ((unsigned)qb[3] << 16);
+      wqn[t][0] = pack4(qa[0], qa[1], qa[2], qa[3]);
+      wqn[t][1] = pack4(qb[0], qb[1], qb[2], qb[3]);
+    }
+    const unsigned h2 = 2u * (unsigned)(k & 1);
+    selA = h2 | (0x0cu << 8) | ((4u + h2) << 16) | (0x0cu << 24);
+    selZ1 = h2 | ((4u + h2) << 8) | 0x0c0c0000u;
+    selZ2 = 0x00000c0cu | (h2 << 16) | ((4u + h2) << 24);
+  }
+
+  // hi/lo bytes of w and the zero-point term of group K, for every row
+  __device__ __forceinline__ void store(const GroupK<BITS>& K, unsigned char (*whi)[128],
+                                        unsigned char (*wlo)[128], int* wbias) const {
+    const int lane = threadIdx.x & 63, k = lane & 15;
+    // s^int pairs matching wq and z^int bytes matching wqn
+    unsigned sA01, sA23, sB01, sB23, zA, zB;
+    if constexpr (BITS == 4) {
+      sA01 = __builtin_amdgcn_perm(0u, K.ws[0], 0x0c020c00u);
+      sA23 = __builtin_amdgcn_perm(0u, K.ws[1], 0x0c020c00u);
+      sB01 = __builtin_amdgcn_perm(0u, K.ws[0], 0x0c030c01u);
+      sB23 = __builtin_amdgcn_perm(0u, K.ws[1], 0x0c030c01u);
+      zA = __builtin_amdgcn_perm(K.wz[1], K.wz[0], 0x06040200u);
+      zB = __builtin_amdgcn_perm(K.wz[1], K.wz[0], 0x07050301u);
+    } else {
+      sA01 = __builtin_amdgcn_perm(K.ws[1], K.ws[0], selA);
+      sA23 = __builtin_amdgcn_perm(K.ws[3], K.ws[2], selA);
+      sB01 = __builtin_amdgcn_perm(K.ws[1], K.ws[0], selA + 0x00010001u);
+      sB23 = __builtin_amdgcn_perm(K.ws[3], K.ws[2], selA + 0x00010001u);
+      zA = __builtin_amdgcn_perm(K.wz[1], K.wz[0], selZ1) |
+           __builtin_amdgcn_perm(K.wz[3], K.wz[2], selZ2);
+      zB = __builtin_amdgcn_perm(K.wz[1], K.wz[0], selZ1 + 0x0101u) |
+           __builtin_amdgcn_perm(K.wz[3], K.wz[2], selZ2 + 0x01010000u);
+    }
+#pragma unroll
+    for (int t = 0; t < kU; ++t) {
+      const int r = (lane >> 4) + 4 * t;
+      const unsigned sp[4] = {sA01, sA23, sB01, sB23};
+      unsigned hx[4], lx[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const u16x2 w = __builtin_bit_cast(u16x2, wq[t][u]) * __builtin_bit_cast(u16x2, sp[u]);
+        hx[u] = __builtin_bit_cast(unsigned, __builtin_bit_cast(s16x2, w) >> (short)7);
+        lx[u] = __builtin_bit_cast(unsigned, w) & 0x007F007Fu;
+      }
+      *reinterpret_cast<uint2*>(&whi[r][8 * k]) =
+          make_uint2(__builtin_amdgcn_perm(hx[1], hx[0], 0x06040200u),
+                     __builtin_amdgcn_perm(hx[3], hx[2], 0x06040200u));
+      *reinterpret_cast<uint2*>(&wlo[r][8 * k]) =
+          make_uint2(__builtin_amdgcn_perm(lx[1], lx[0], 0x06040200u),
+                     __builtin_amdgcn_perm(lx[3], lx[2], 0x06040200u));
+      // zero-point term sum_c q_c z_c of row r: the unit's 8 channels, then
+      // the 16 units of the row (one DPP row; exact: |sum| < 2^24)
+      const int bp = __builtin_amdgcn_sdot4(wqn[t][0], (int)zA,
+                                            __builtin_amdgcn_sdot4(wqn[t][1], (int)zB, 0, false),
+                                            false);
+      wbias[r] = row_sum_i<16>(bp);  // every lane of the row: the same value
+    }
+  }
+};
+
+// S^T = K^{q1} q^T on the MFMA: lane (n, g4), register r of sv[mb] holds row n,
+// token 16*mb + 4*g4 + r.
+template <int BITS>
+__device__ __forceinline__ void decode_qk(const GroupK<BITS>& K, const v4i (&bhi)[2],
+                                          const v4i (&blo)[2], int bias, int4 (&sv)[4]) {
+#pragma unroll
+  for (int mb = 0; mb < 4; ++mb) {
+    v4i kop[2];
+    if (BITS == 4) {
+      unsigned u[8];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        u[2 * w] = K.kraw[mb][w] & 0x0F0F0F0Fu;
+        u[2 * w + 1] = (K.kraw[mb][w] >> 4) & 0x0F0F0F0Fu;
+      }
+      kop[0] = v4i{(int)u[0], (int)u[1], (int)u[2], (int)u[3]};
+      kop[1] = v4i{(int)u[4], (int)u[5], (int)u[6], (int)u[7]};
+    } else {
+#pragma unroll
+      for (int w = 0; w < 2; ++w)
+        kop[w] = v4i{(int)(K.kraw[mb][w] & 0x03030303u),
+                     (int)((K.kraw[mb][w] >> 2) & 0x03030303u),
+                     (int)((K.kraw[mb][w] >> 4) & 0x03030303u),
+                     (int)((K.kraw[mb][w] >> 6) & 0x03030303u)};
+    }
+    v4i lo = v4i{bias, bias, bias, bias};
+    v4i hi = {};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      lo = mfma16x16x64(kop[ks], blo[ks], lo);
+      hi = mfma16x16x64(kop[ks], bhi[ks], hi);
+    }
+    sv[mb] = make_int4((hi[0] << 7) + lo[0], (hi[1] << 7) + lo[1], (hi[2] << 7) + lo[2],
+                       (hi[3] << 7) + lo[3]);
+  }
+}
+
+// PV B-operand: the 16 codes of channel 16*cb + n in page g4.
+template <int BITS>
+__device__ __forceinline__ v4i v_codes(const GroupV<BITS>& V, int cb) {
+  if (BITS == 4) {
+    const unsigned x0 = V.vraw[cb][0], x1 = V.vraw[cb][BITS / 2 - 1];
+    return v4i{(int)(x0 & 0x0F0F0F0Fu), (int)((x0 >> 4) & 0x0F0F0F0Fu), (int)(x1 & 0x0F0F0F0Fu),
+               (int)((x1 >> 4) & 0x0F0F0F0Fu)};
+  } else {
+    const unsigned x = V.vraw[cb][0];
+    return v4i{(int)(x & 0x03030303u), (int)((x >> 2) & 0x03030303u),
+               (int)((x >> 4) & 0x03030303u), (int)((x >> 6) & 0x03030303u)};
+  }
+}
+
 template <int GP, int BITS, bool kTrace>
 __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>& L, int b, int kh,
                                               int g0, int g1, int head_off, float& mrow, float& lpart, float& beta,
                                               float (&O)[GP][2], float sq_row, int trow) {
   constexpr int LPR = 64 / GP;  // lanes per compact softmax row
-  constexpr int d = BITS == 4 ? 2 : 4;
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g4 = lane >> 4;
   const int rr = lane / LPR, cc = lane % LPR;
@@ -349,40 +598,8 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
   int* const obase = orows ? &L.obuf[n][4 * g4] : &L.odum[odi][0];
   const int ostep = orows ? 16 * kObufStride<GP> : 0;
 
-  // ---- w = q * s^int, written by all lanes ------------------------------
-  // The QK^T B-operand of lane (n, g4), k-step ks, is 16 bytes: dword j, byte
-  // i holds channel 32*g4 + c0 + d*i with c0 = 16ks + 8(j>>1) + (j&1) (int4)
-  // or 16ks + j (int2), the order the K codes unpack to.  Only GP of the 16
-  // rows n are real, so instead of every lane building its own 32 values,
-  // lane L builds those of unit U = L + 64t: row U >> 4, 8 channels given by
-  // k = U & 15 -- dwords j = 2h, 2h+1 (h = k & 1) of block (g4 = k >> 2,
-  // ks = (k >> 1) & 1) -- and writes their hi/lo bytes to byte 8k of the row.
-  constexpr int kU = GP <= 4 ? 1 : GP / 4;  // writer units per lane
-  const int k = lane & 15;
-  const int cA = BITS == 4 ? 8 * k : 16 * (k >> 1) + 2 * (k & 1);  // channel of dword 2h, byte 0
-  unsigned wq[kU][4];  // 16-bit q pairs (A0,A1) (A2,A3) (B0,B1) (B2,B3)
-  int wqn[kU][2];      // the q bytes of dword A (= 2h) and B (= 2h + 1)
-#pragma unroll
-  for (int t = 0; t < kU; ++t) {
-    const int r = (lane >> 4) + 4 * t;
-    int qa[4], qb[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      qa[i] = L.qbuf[r][cA + d * i];
-      qb[i] = L.qbuf[r][cA + 1 + d * i];
-    }
-    wq[t][0] = ((unsigned)qa[0] & 0xffffu) | ((unsigned)qa[1] << 16);
-    wq[t][1] = ((unsigned)qa[2] & 0xffffu) | ((unsigned)qa[3] << 16);
-    wq[t][2] = ((unsigned)qb[0] & 0xffffu) | ((unsigned)qb[1] << 16);
-    wq[t][3] = ((unsigned)qb[2] & 0xffffu) | ((unsigned)qb[3] << 16);
-    wqn[t][0] = pack4(qa[0], qa[1], qa[2], qa[3]);
-    wqn[t][1] = pack4(qb[0], qb[1], qb[2], qb[3]);
-  }
-  // int2: byte selectors of channel 2h (+1) in the four dwords of the block
-  const unsigned h2 = 2u * (unsigned)(k & 1);
-  const unsigned selA = h2 | (0x0cu << 8) | ((4u + h2) << 16) | (0x0cu << 24);
-  const unsigned selZ1 = h2 | ((4u + h2) << 8) | 0x0c0c0000u;
-  const unsigned selZ2 = 0x00000c0cu | (h2 << 16) | ((4u + h2) << 24);
+  QueryW<GP, BITS> Wq;
+  Wq.load(L.qbuf);
   const int wrow = min(n, kWRows<GP> - 1);  // row this lane reads (unused rows: any)
 
   const int* bt = a.block_table + (long)b * 4 * a.max_groups;
@@ -393,8 +610,20 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
   // issues K of the next group first and V of its own group after its QK^T
   // MFMAs (V is not held during the QK^T phase); the softmax covers the V
   // latency.
+  // (more than one row leaves no registers for the table)
+  constexpr bool kTab = GP == 1;
+  GroupTab T;
+  if constexpr (kTab) load_tab<1>(a, kh, bt, gt, g0, g1, T);
+  auto next_k = [&](int g, GroupK<BITS>& K) {
+    if constexpr (kTab) {
+      if (g != g0 && ((g - g0) & 63) == 0) load_tab<1>(a, kh, bt, gt, g, g1, T);
+      load_k<BITS>(a, kh, head_off, T, (g - g0) & 63, K);
+    } else {
+      load_k<BITS>(a, kh, head_off, bt, gt, g, g < g1, K);
+    }
+  };
   GroupK<BITS> KA, KB;
-  load_k<BITS>(a, kh, head_off, bt, gt, g0, g0 < g1, KA);
+  next_k(g0, KA);
   // Issue priority (s_setprio) is highest from a group's start until its V
   // loads are out, and for the K prefetch, lower in the softmax and lowest in
   // the PV and update steps: a wave on its way to a load goes ahead of the
@@ -403,49 +632,7 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
   auto process = [&](const GroupK<BITS>& cur, int g) {
     if (cur.ok) {
       __builtin_amdgcn_s_setprio(2);
-      // s^int pairs matching wq and z^int bytes matching wqn (see above)
-      unsigned sA01, sA23, sB01, sB23, zA, zB;
-      if constexpr (BITS == 4) {
-        sA01 = __builtin_amdgcn_perm(0u, cur.ws[0], 0x0c020c00u);
-        sA23 = __builtin_amdgcn_perm(0u, cur.ws[1], 0x0c020c00u);
-        sB01 = __builtin_amdgcn_perm(0u, cur.ws[0], 0x0c030c01u);
-        sB23 = __builtin_amdgcn_perm(0u, cur.ws[1], 0x0c030c01u);
-        zA = __builtin_amdgcn_perm(cur.wz[1], cur.wz[0], 0x06040200u);
-        zB = __builtin_amdgcn_perm(cur.wz[1], cur.wz[0], 0x07050301u);
-      } else {
-        sA01 = __builtin_amdgcn_perm(cur.ws[1], cur.ws[0], selA);
-        sA23 = __builtin_amdgcn_perm(cur.ws[3], cur.ws[2], selA);
-        sB01 = __builtin_amdgcn_perm(cur.ws[1], cur.ws[0], selA + 0x00010001u);
-        sB23 = __builtin_amdgcn_perm(cur.ws[3], cur.ws[2], selA + 0x00010001u);
-        zA = __builtin_amdgcn_perm(cur.wz[1], cur.wz[0], selZ1) |
-             __builtin_amdgcn_perm(cur.wz[3], cur.wz[2], selZ2);
-        zB = __builtin_amdgcn_perm(cur.wz[1], cur.wz[0], selZ1 + 0x0101u) |
-             __builtin_amdgcn_perm(cur.wz[3], cur.wz[2], selZ2 + 0x01010000u);
-      }
-#pragma unroll
-      for (int t = 0; t < kU; ++t) {
-        const int r = (lane >> 4) + 4 * t;
-        const unsigned sp[4] = {sA01, sA23, sB01, sB23};
-        unsigned hx[4], lx[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const u16x2 w = __builtin_bit_cast(u16x2, wq[t][u]) * __builtin_bit_cast(u16x2, sp[u]);
-          hx[u] = __builtin_bit_cast(unsigned, __builtin_bit_cast(s16x2, w) >> (short)7);
-          lx[u] = __builtin_bit_cast(unsigned, w) & 0x007F007Fu;
-        }
-        *reinterpret_cast<uint2*>(&L.whi[r][8 * k]) =
-            make_uint2(__builtin_amdgcn_perm(hx[1], hx[0], 0x06040200u),
-                       __builtin_amdgcn_perm(hx[3], hx[2], 0x06040200u));
-        *reinterpret_cast<uint2*>(&L.wlo[r][8 * k]) =
-            make_uint2(__builtin_amdgcn_perm(lx[1], lx[0], 0x06040200u),
-                       __builtin_amdgcn_perm(lx[3], lx[2], 0x06040200u));
-        // zero-point term sum_c q_c z_c of row r: the unit's 8 channels, then
-        // the 16 units of the row (one DPP row; exact: |sum| < 2^24)
-        const int bp = __builtin_amdgcn_sdot4(wqn[t][0], (int)zA,
-                                              __builtin_amdgcn_sdot4(wqn[t][1], (int)zB, 0, false),
-                                              false);
-        L.wbias[r] = row_sum_i<16>(bp);  // every lane of the row: the same value
-      }
+      Wq.store(cur, L.whi, L.wlo, L.wbias);
       wave_sync();
       v4i bhi[2], blo[2];
 #pragma unroll
@@ -456,36 +643,7 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
       const int bias = L.wbias[wrow];
       // ---- S^T = K^{q1} q^T on the MFMA, scores to LDS -----------------
       int4 sv[4];
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        v4i kop[2];
-        if (BITS == 4) {
-          unsigned u[8];
-#pragma unroll
-          for (int w = 0; w < 4; ++w) {
-            u[2 * w] = cur.kraw[mb][w] & 0x0F0F0F0Fu;
-            u[2 * w + 1] = (cur.kraw[mb][w] >> 4) & 0x0F0F0F0Fu;
-          }
-          kop[0] = v4i{(int)u[0], (int)u[1], (int)u[2], (int)u[3]};
-          kop[1] = v4i{(int)u[4], (int)u[5], (int)u[6], (int)u[7]};
-        } else {
-#pragma unroll
-          for (int w = 0; w < 2; ++w)
-            kop[w] = v4i{(int)(cur.kraw[mb][w] & 0x03030303u),
-                         (int)((cur.kraw[mb][w] >> 2) & 0x03030303u),
-                         (int)((cur.kraw[mb][w] >> 4) & 0x03030303u),
-                         (int)((cur.kraw[mb][w] >> 6) & 0x03030303u)};
-        }
-        v4i lo = v4i{bias, bias, bias, bias};
-        v4i hi = {};
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          lo = mfma16x16x64(kop[ks], blo[ks], lo);
-          hi = mfma16x16x64(kop[ks], bhi[ks], hi);
-        }
-        sv[mb] = make_int4((hi[0] << 7) + lo[0], (hi[1] << 7) + lo[1], (hi[2] << 7) + lo[2],
-                           (hi[3] << 7) + lo[3]);
-      }
+      decode_qk<BITS>(cur, bhi, blo, bias, sv);
       GroupV<BITS> cv;
       load_v<BITS>(a, kh, head_off, cur, cv);
       __builtin_amdgcn_s_setprio(1);
@@ -572,17 +730,6 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
       __builtin_amdgcn_s_setprio(0);
       // ---- O = Q(P~) V on the raw codes (A = P rows, B = V codes) -------
       const v4i pop = *reinterpret_cast<const v4i*>(&L.pbuf[nrow][16 * g4]);
-      auto vop_of = [&](int cb) {
-        if (BITS == 4) {
-          const unsigned x0 = cv.vraw[cb][0], x1 = cv.vraw[cb][BITS / 2 - 1];
-          return v4i{(int)(x0 & 0x0F0F0F0Fu), (int)((x0 >> 4) & 0x0F0F0F0Fu),
-                     (int)(x1 & 0x0F0F0F0Fu), (int)((x1 >> 4) & 0x0F0F0F0Fu)};
-        } else {
-          const unsigned x = cv.vraw[cb][0];
-          return v4i{(int)(x & 0x03030303u), (int)((x >> 2) & 0x03030303u),
-                     (int)((x >> 4) & 0x03030303u), (int)((x >> 6) & 0x03030303u)};
-        }
-      };
       // lane (n, g4), register r <-> row 4*g4 + r, channel 16*cb + n
       auto store = [&](int cb, const v4i& acc) {
         if (GP >= 4) {
@@ -598,8 +745,8 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
       // one's result is stored
 #pragma unroll
       for (int cb = 0; cb < 8; cb += 2) {
-        const v4i acc0 = mfma16x16x64(pop, vop_of(cb), v4i{});
-        const v4i acc1 = mfma16x16x64(pop, vop_of(cb + 1), v4i{});
+        const v4i acc0 = mfma16x16x64(pop, v_codes<BITS>(cv, cb), v4i{});
+        const v4i acc1 = mfma16x16x64(pop, v_codes<BITS>(cv, cb + 1), v4i{});
         store(cb, acc0);
         store(cb + 1, acc1);
       }
@@ -653,23 +800,397 @@ __device__ __forceinline__ void decode_groups(const DecodeArgs& a, DecodeLds<GP>
   };
   for (int g = g0; g < g1; g += 2) {
     __builtin_amdgcn_s_setprio(2);
-    load_k<BITS>(a, kh, head_off, bt, gt, g + 1, g + 1 < g1, KB);
+    next_k(g + 1, KB);
     __builtin_amdgcn_s_setprio(0);
     process(KA, g);
     if (g + 1 < g1) {
       __builtin_amdgcn_s_setprio(2);
-      load_k<BITS>(a, kh, head_off, bt, gt, g + 2, g + 2 < g1, KA);
+      next_k(g + 2, KA);
       __builtin_amdgcn_s_setprio(0);
       process(KB, g + 1);
     }
   }
 }
 
-// kTrace = true only for the test hook that also stores one group's integers
-// (the production instances carry no trace code).
-template <int GP, bool kTrace>
+// ---- cooperating waves --------------------------------------------------
+// A work-group of W waves takes one chunk W consecutive groups at a time, a
+// group per wave, with the results of one wave going through the groups in
+// order, bit for bit:
+//  * every wave forms its group's scores and row maxima; after a barrier each
+//    wave forms the running maximum before its group, and the rescale factor
+//    of every group of the step, from the maxima of all of them;
+//  * SAS, Q(P~) and the integer PV of the group follow, and go to LDS;
+//  * after a second barrier the waves share the update: each holds a slice of
+//    the accumulator (GP / W rows, or half a row) and adds the step's groups
+//    to it in order; l and beta are kept by every wave.
+// The loads of a step leave early: K of the next step behind the QK^T that
+// frees its registers, V ahead of the QK^T.
+constexpr int kORow = 132;  // ints per row: the four rows of a lane in distinct bank groups
+
+template <int GP>
+struct CoopWave {
+  union {
+    struct {  // w = q * s^int, read back before the scores are stored
+      __attribute__((aligned(16))) unsigned char whi[kWRows<GP>][128];
+      __attribute__((aligned(16))) unsigned char wlo[kWRows<GP>][128];
+    };
+    __attribute__((aligned(16))) int sbuf[GP][kSbufStride];  // scores, row n
+  };
+  union {
+    signed char qbuf[kWRows<GP>][128];  // the int8 query rows (read before the first step)
+    __attribute__((aligned(16))) int orow[GP][kORow];  // sums Q(P~) code of the group
+  };
+  __attribute__((aligned(16))) unsigned char pbuf[GP + 1][64];  // Q(P~), as in DecodeLds
+  float sq[16];
+  int wbias[kWRows<GP>];
+  unsigned vsz[64];  // V scales, then zeros, of the 128 channels
+  float rs[64];      // each lane's share of the row sums of P~
+  float2 rowp[GP];   // s_P s_V, sum Q(P~)
+};
+
+template <int GP, int W>
+struct CoopLds {
+  float lut[8];
+  int ok[W];  // the wave's group is attended
+  __attribute__((aligned(16))) float gmax[GP][W];
+  CoopWave<GP> wave[W];
+};
+
+// Slice of the GP x 128 accumulator that wave w holds: kSRows rows of which
+// lane L has channels 2L, 2L + 1, or (GP < W) one half row.
+template <int GP, int W>
+struct Slice {
+  static constexpr int kRows = GP >= W ? GP / W : 1;
+  static constexpr int kCh = GP >= W ? 2 : 1;
+};
+
+template <int GP, int BITS, int W, bool kTrace>
+__device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>& LW, int w, int b,
+                                            int kh, int g0, int g1, int head_off, float& mrow,
+                                            float& lpart, float& beta,
+                                            float (&O)[Slice<GP, W>::kRows][Slice<GP, W>::kCh],
+                                            int trow) {
+  constexpr int LPR = 64 / GP;
+  constexpr int kRows = Slice<GP, W>::kRows, kCh = Slice<GP, W>::kCh;
+  CoopWave<GP>& L = LW.wave[w];
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, g4 = lane >> 4;
+  const int rr = lane / LPR, cc = lane % LPR;
+  const int nrow = min(n, GP), wrow = min(n, kWRows<GP> - 1);
+  const int row0 = kCh == 2 ? w * kRows : w >> 1;        // the slice
+  const int ch = kCh == 2 ? 2 * lane : 64 * (w & 1) + lane;
+  const bool holds = row0 < GP;                           // wave-uniform
+  const int* bt = a.block_table + (long)b * 4 * a.max_groups;
+  const int* gt = a.group_table + (long)b * a.max_groups;
+
+  GroupTab T;
+  GroupK<BITS> K;
+  load_tab<W>(a, kh, bt, gt, g0 + w, g1, T);
+  auto next_k = [&](int st) {  // the wave's group of step st
+    if (st != 0 && (st & 63) == 0) load_tab<W>(a, kh, bt, gt, g0 + w + W * st, g1, T);
+    load_k<BITS>(a, kh, head_off, T, st & 63, K);
+  };
+  next_k(0);  // on its way while the query is quantized
+  decode_quant_q<GP, kTrace>(a, L.sq, L.qbuf, b, kh, w == 0 ? trow : -1);
+  wave_sync();
+  const float sq_row = L.sq[rr];
+  QueryW<GP, BITS> Wq;
+  Wq.load(L.qbuf);
+  wave_sync();  // orow takes qbuf's place
+
+  const int nst = ceil_div(g1 - g0, W);  // work-group uniform
+  for (int st = 0; st < nst; ++st) {
+    const int g = g0 + w + W * st;
+    const bool ok = K.ok;
+    const float skg = K.skg, svg = K.svg;
+    const bool trace_g = kTrace && trow >= 0 && g == a.tr_g;  // wave-uniform
+    float p[GP], smax = -INFINITY;
+    GroupV<BITS> cv;
+    if (ok) {
+      load_v<BITS>(a, kh, head_off, K, cv);
+      __builtin_amdgcn_s_setprio(2);
+      Wq.store(K, L.whi, L.wlo, L.wbias);
+      wave_sync();
+      v4i bhi[2], blo[2];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        bhi[ks] = *reinterpret_cast<const v4i*>(&L.whi[wrow][32 * g4 + 16 * ks]);
+        blo[ks] = *reinterpret_cast<const v4i*>(&L.wlo[wrow][32 * g4 + 16 * ks]);
+      }
+      const int bias = L.wbias[wrow];
+      wave_sync();  // sbuf takes the place of whi and wlo
+      int4 sv[4];
+      decode_qk<BITS>(K, bhi, blo, bias, sv);
+      next_k(st + 1);
+      __builtin_amdgcn_s_setprio(1);
+      if (n < GP) {
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+          *reinterpret_cast<int4*>(&L.sbuf[n][16 * mb + 4 * g4]) = sv[mb];
+      }
+      if (trace_g && n == trow) {
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+          reinterpret_cast<int4*>(a.trace + TURBO_TRACE_S)[4 * mb + g4] = sv[mb];
+      }
+      wave_sync();
+      // compact scores: lane (rr, cc) holds tokens cc*GP .. +GP-1 of row rr
+      int si[GP];
+      if (GP >= 4) {
+#pragma unroll
+        for (int e = 0; e < GP; e += 4) {
+          const int4 t = *reinterpret_cast<const int4*>(&L.sbuf[rr][cc * GP + e]);
+          si[e] = t.x; si[e + 1] = t.y; si[e + 2] = t.z; si[e + 3] = t.w;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < GP; ++e) si[e] = L.sbuf[rr][cc * GP + e];
+      }
+      const float c = (sq_row * skg) * a.sm_scale;
+      int imax = si[0];
+#pragma unroll
+      for (int e = 0; e < GP; ++e) {
+        p[e] = (float)si[e] * c;
+        imax = max(imax, si[e]);
+      }
+      smax = (float)row_max_i<LPR>(imax) * c;  // c >= 0, monotonic roundings
+    } else {
+      next_k(st + 1);
+    }
+    if (cc == 0) LW.gmax[rr][w] = smax;
+    if (lane == 0) LW.ok[w] = ok;
+    __syncthreads();
+
+    // ---- running maximum and rescale factors of the step's groups ---------
+    float gm[W], f[W], mnew = mrow;
+#pragma unroll
+    for (int i = 0; i < W; i += 2) {
+      const float2 t = *reinterpret_cast<const float2*>(&LW.gmax[rr][i]);
+      gm[i] = t.x; gm[i + 1] = t.y;
+    }
+    const unsigned okm =
+        (unsigned)__builtin_amdgcn_ballot_w64(LW.ok[lane & (W - 1)] != 0) & ((1u << W) - 1);
+    float top = gm[0];
+#pragma unroll
+    for (int i = 1; i < W; ++i) top = fmaxf(top, gm[i]);
+    // no row moves its maximum in this step: every factor is 1 (e^0)
+    const bool moved = __builtin_amdgcn_ballot_w64(top > mrow) != 0;
+    if (moved) {
+      // the W factors side by side (no branch, one table latency for all)
+      float m = mrow;
+#pragma unroll
+      for (int i = 0; i < W; ++i) {
+        const float mi = fmaxf(m, gm[i]);
+        f[i] = sas_y(mi - m, LW.lut);  // 0 when m = -inf
+        f[i] = mi > m ? f[i] : 1.0f;
+        mnew = i <= w ? mi : mnew;
+        m = mi;
+      }
+      mrow = m;
+    }
+    if (ok) {
+      float rs = 0.0f;
+      int pbits = 0;  // the maximum of the p >= 0, on their bits (same order)
+#pragma unroll
+      for (int e = 0; e < GP; ++e) {
+        p[e] = sas_y(mnew - p[e], LW.lut);
+        rs += p[e];
+        pbits = max(pbits, __float_as_int(p[e]));
+      }
+      L.rs[lane] = rs;
+      const float pmax = __int_as_float(row_max_i<LPR>(pbits));
+      // Q(P~) with the row's scale pmax/119 (pmax = 0: inv = 0, adds nothing)
+      const float inv = pmax > 0.0f ? kQmax / pmax : 0.0f;
+      int ps = 0;
+#pragma unroll
+      for (int e = 0; e < GP; ++e) {
+        const int code = rne_bits(p[e], inv) & 0xff;
+        ps += code;
+        const int t = cc * GP + e;  // token of the group
+        L.pbuf[rr][16 * (t >> 4) + vpos<BITS>(t & 15)] = (unsigned char)code;
+        if (trace_g && rr == trow) a.trace[TURBO_TRACE_P + t] = (unsigned char)code;
+      }
+      if (trace_g && rr == trow && cc == 0)
+        *reinterpret_cast<float*>(a.trace + TURBO_TRACE_PMAX) = pmax;
+      const int psum = row_sum_i<LPR>(ps);
+      if (cc == 0)
+        L.rowp[rr] = make_float2((pmax * (1.0f / kQmax)) * svg, __int_as_float(psum));
+      wave_sync();
+      __builtin_amdgcn_s_setprio(0);
+      const v4i pop = *reinterpret_cast<const v4i*>(&L.pbuf[nrow][16 * g4]);
+      // lane (n, g4), register r <-> row 4*g4 + r, channel 16*cb + n
+#pragma unroll
+      for (int cb = 0; cb < 8; cb += 2) {
+        const v4i acc0 = mfma16x16x64(pop, v_codes<BITS>(cv, cb), v4i{});
+        const v4i acc1 = mfma16x16x64(pop, v_codes<BITS>(cv, cb + 1), v4i{});
+        if (4 * g4 < GP) {
+#pragma unroll
+          for (int r = 0; r < (GP < 4 ? GP : 4); ++r) {
+            L.orow[4 * g4 + r][16 * cb + n] = acc0[r];
+            L.orow[4 * g4 + r][16 * cb + 16 + n] = acc1[r];
+          }
+        }
+      }
+      if ((lane & 1) == 0) {
+        L.vsz[lane >> 1] = cv.vs4;
+        L.vsz[32 + (lane >> 1)] = cv.vz4;
+      }
+    }
+    __syncthreads();
+
+    // ---- the step's groups, in order ---------------------------------------
+    // O += g * (s * sum P*code + z * sum P) of group i, g = s_P s_V / beta
+    auto add_group = [&](int i, float2 rp, float rbeta) {
+      const CoopWave<GP>& X = LW.wave[i];
+      const float gsc = rp.x * rbeta;
+      const unsigned char* vb = reinterpret_cast<const unsigned char*>(X.vsz);
+      int sc[kCh], zc[kCh];
+      if constexpr (kCh == 2) {
+        const unsigned s2 = *reinterpret_cast<const unsigned short*>(vb + ch);
+        const unsigned z2 = *reinterpret_cast<const unsigned short*>(vb + 128 + ch);
+        sc[0] = (int)(s2 & 0xffu);
+        sc[kCh - 1] = (int)(s2 >> 8);
+        zc[0] = (int)(int8_t)(z2 & 0xffu);
+        zc[kCh - 1] = (int)(int8_t)(z2 >> 8);
+      } else {
+        sc[0] = (int)vb[ch];
+        zc[0] = (int)(int8_t)vb[128 + ch];
+      }
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        const int src = (row0 + r) * LPR;
+        const float gr = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gsc), src));
+        const int psum = __builtin_amdgcn_readlane(__float_as_int(rp.y), src);
+        int acc[kCh];
+        if constexpr (kCh == 2) {
+          const int2 t = *reinterpret_cast<const int2*>(&X.orow[row0 + r][ch]);
+          acc[0] = t.x;
+          acc[kCh - 1] = t.y;
+        } else {
+          acc[0] = X.orow[row0][ch];
+        }
+#pragma unroll
+        for (int c2 = 0; c2 < kCh; ++c2) {
+          // exact int32 PV of Algorithm 2 (every factor fits 24 bits)
+          const int pv = __mul24(sc[c2], acc[c2]) + __mul24(zc[c2], psum);
+          O[r][c2] = __builtin_fmaf(gr, (float)pv, O[r][c2]);
+          if (kTrace && trow == row0 + r && g0 + W * st + i == a.tr_g)
+            reinterpret_cast<int*>(a.trace + TURBO_TRACE_PV)[ch + c2] = pv;
+        }
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      if (!((okm >> i) & 1u)) continue;  // work-group uniform
+      const float alpha = moved ? f[i] : 1.0f;
+      lpart = alpha * lpart + LW.wave[i].rs[lane];
+      // rescale: O = beta * Ost; renormalize when beta underflows / is 0
+      float nbeta = beta * alpha;
+      if (__builtin_amdgcn_ballot_w64(nbeta < 0x1p-64f) != 0) {  // rare, the same in every wave
+        asm volatile("");
+        if (holds) {
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            const float rf = __int_as_float(
+                __builtin_amdgcn_readlane(__float_as_int(nbeta), (row0 + r) * LPR));
+#pragma unroll
+            for (int c2 = 0; c2 < kCh; ++c2) O[r][c2] *= rf;
+          }
+        }
+        nbeta = 1.0f;
+      }
+      beta = nbeta;
+      if (holds) add_group(i, LW.wave[i].rowp[rr], __builtin_amdgcn_rcpf(beta));
+    }
+  }
+}
+
+template <int GP, int W, bool kTrace>
 __device__ void decode_tail_body(const DecodeArgs& a, int bx);  // kv_tail.hip
 
+// W waves per (b, KV head, chunk of groups).
+template <int GP, int W, bool kTrace>
+__global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decode_coop(
+    DecodeArgs a) {
+  const int nmain = a.B * a.Hkv * a.nsplit;
+  if ((int)blockIdx.x >= nmain) {
+    decode_tail_body<GP, W, kTrace>(a, (int)blockIdx.x - nmain);
+    return;
+  }
+  __shared__ CoopLds<GP, W> LW;
+  constexpr int LPR = 64 / GP;
+  constexpr int kRows = Slice<GP, W>::kRows, kCh = Slice<GP, W>::kCh;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s = blockIdx.x % a.nsplit;
+  const int kh = (blockIdx.x / a.nsplit) % a.Hkv;
+  const int b = blockIdx.x / (a.nsplit * a.Hkv);
+  const int lane = threadIdx.x & 63;
+  const int rr = lane / LPR, cc = lane % LPR;
+  const int G = a.G;
+  const DecodeSeq sq_ = decode_seq(a, b);
+  const int g0 = s * sq_.split;
+  const int g1 = min(sq_.ng, g0 + sq_.split);
+  if (g1 <= g0) {  // no group of this sequence in the chunk
+    if (s == 0 && sq_.nparts == 0) decode_write_empty(a, b, kh);
+    return;
+  }
+  if (threadIdx.x < 8) LW.lut[lane] = kLut[lane];  // read behind the first step's barrier
+  const int bits = ((a.int2_mask >> kh) & 1ull) ? 2 : 4;
+  const int head_off = 512 * (4 * kh - 2 * __popcll(a.int2_mask & ((1ull << kh) - 1ull)));
+  // traced row of this work-group (-1: none), whose chunk holds group tr_g
+  const int trow = kTrace && b == a.tr_b && kh == a.tr_h / G && g0 <= a.tr_g && a.tr_g < g1
+                       ? a.tr_h % G : -1;
+  float O[kRows][kCh] = {};
+  float mrow = -INFINITY, lpart = 0.0f, beta = 1.0f;
+  if (bits == 4)
+    decode_coop<GP, 4, W, kTrace>(a, LW, w, b, kh, g0, g1, head_off, mrow, lpart, beta, O, trow);
+  else
+    decode_coop<GP, 2, W, kTrace>(a, LW, w, b, kh, g0, g1, head_off, mrow, lpart, beta, O, trow);
+
+  // every wave holds m, l and beta of all rows and its slice of O
+  const float l = row_sum<LPR>(lpart);
+  const bool one = sq_.nparts == 1;  // the only state (chunk 0): O / l and L directly
+  const float fo = one ? beta / l : beta;
+  const int row0 = kCh == 2 ? w * kRows : w >> 1;
+  const int ch = kCh == 2 ? 2 * lane : 64 * (w & 1) + lane;
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    if (row0 + r >= G) break;  // wave-uniform
+    const float fr =
+        __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fo), (row0 + r) * LPR));
+    const long bh = (long)b * a.Hq + kh * G + row0 + r;
+    if (one) {
+      _Float16* o = reinterpret_cast<_Float16*>(a.o) + bh * 128 + ch;
+      if constexpr (kCh == 2) {
+        _Float16 h2[2] = {(_Float16)(O[r][0] * fr), (_Float16)(O[r][kCh - 1] * fr)};
+        *reinterpret_cast<unsigned*>(o) = __builtin_bit_cast(unsigned, h2);
+      } else {
+        float x = O[r][0] * fr;
+        asm("" : "+v"(x));  // product and rounding apart, as where two are packed
+        *o = (_Float16)x;
+      }
+    } else {
+      float* ws = a.ws + (bh * a.nws + s) * kWsStride + kWsO + ch;
+      if constexpr (kCh == 2)
+        *reinterpret_cast<float2*>(ws) = make_float2(O[r][0] * fr, O[r][kCh - 1] * fr);
+      else
+        *ws = O[r][0] * fr;
+    }
+  }
+  if (w == 0 && cc == 0 && rr < G) {
+    const long bh = (long)b * a.Hq + kh * G + rr;
+    if (!one) {
+      float* ws = a.ws + (bh * a.nws + s) * kWsStride;
+      ws[0] = mrow;
+      ws[1] = l;
+    } else if (a.lse) {
+      a.lse[bh] = mrow + logf(l);
+    }
+  }
+}
+
+// kTrace = true only for the test hook that also stores one group's integers
+// (the production instances carry no trace code).
 // One wave per (b, KV head, chunk of groups); with several chunks each
 // writes its state to the workspace and k_decode_combine merges them.
 template <int GP, bool kTrace>
@@ -677,7 +1198,7 @@ __global__ __launch_bounds__(64, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decod
   // the last B * Hkv work-groups (when there is a buffer): its chunk
   const int nmain = a.B * a.Hkv * a.nsplit;
   if ((int)blockIdx.x >= nmain) {
-    decode_tail_body<GP, kTrace>(a, (int)blockIdx.x - nmain);
+    decode_tail_body<GP, 1, kTrace>(a, (int)blockIdx.x - nmain);
     return;
   }
   __shared__ DecodeLds<GP> L;
@@ -687,7 +1208,6 @@ __global__ __launch_bounds__(64, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decod
   constexpr int LPR = 64 / GP;
   const int lane = threadIdx.x & 63;
   if (lane < 8) L.lut[lane] = kLut[lane];
-  const int n = lane & 15, g4 = lane >> 4;
   const int rr = lane / LPR, cc = lane % LPR;
   const int G = a.G;
 
@@ -707,51 +1227,10 @@ __global__ __launch_bounds__(64, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decod
     const int bits = ((a.int2_mask >> kh) & 1ull) ? 2 : 4;
     const int head_off = 512 * (4 * kh - 2 * __popcll(a.int2_mask & ((1ull << kh) - 1ull)));
 
-    // ---- q -> int8 per (b, query head) (Algorithm 2; eq. step1bpq) -------
-    // lane (n, g4) holds channels 32*g4 .. 32*g4+31 of row n (zero if n >= G)
-    int q8w[8];
-    {
-      const bool rowok = n < G;
-      uint4 raw[4];
-      float amax = 0.0f;
-      const uint4* src = a.q + ((long)b * a.Hq + kh * G + (rowok ? n : 0)) * 16;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        raw[u] = rowok ? src[4 * g4 + u] : make_uint4(0, 0, 0, 0);
-        f16x8_t hv = __builtin_bit_cast(f16x8_t, raw[u]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf((float)hv[e]));
-      }
-      amax = max_xor16(amax);
-      amax = max_xor32(amax);
-      float inv = 0.0f, sq = 0.0f;
-      if (amax > 0.0f) {
-        sq = amax / kQmax;
-        inv = kQmax / amax;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        f16x8_t hv = __builtin_bit_cast(f16x8_t, raw[u]);
-        int qv[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qv[e] = rne_mul((float)hv[e], inv);
-        q8w[2 * u] = pack4(qv[0], qv[1], qv[2], qv[3]);
-        q8w[2 * u + 1] = pack4(qv[4], qv[5], qv[6], qv[7]);
-      }
-      if (g4 == 0) L.sq[n] = sq;
-      if (n < kWRows<GP>) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) *reinterpret_cast<int*>(&L.qbuf[n][32 * g4 + 4 * i]) = q8w[i];
-      }
-    }
     // traced row of this wave (-1: none); the wave whose chunk holds group tr_g
     const int trow = kTrace && b == a.tr_b && kh == a.tr_h / G && g0 <= a.tr_g && a.tr_g < g1
                          ? a.tr_h % G : -1;
-    if (trow >= 0 && n == trow) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) reinterpret_cast<int*>(a.trace + TURBO_TRACE_Q8)[8 * g4 + i] = q8w[i];
-      if (g4 == 0) *reinterpret_cast<float*>(a.trace + TURBO_TRACE_SQ) = L.sq[n];
-    }
+    decode_quant_q<GP, kTrace>(a, L.sq, L.qbuf, b, kh, trow);
     wave_sync();
     const float sq_row = L.sq[rr];
 
@@ -852,25 +1331,71 @@ __global__ __launch_bounds__(64) void k_decode_combine(DecodeArgs a) {
   if (a.lse && lane == 0) a.lse[bh] = mstar + logf(den);
 }
 
+template <int W, bool kTrace>
+static void launch_decode(const DecodeArgs& a, int total, hipStream_t stream) {
+  const dim3 grid(total), block(64 * W);
+  if constexpr (W == 1) {  // at most four rows
+    if (a.G <= 1)
+      hipLaunchKernelGGL((k_attn_decode<1, kTrace>), grid, block, 0, stream, a);
+    else if (a.G <= 2)
+      hipLaunchKernelGGL((k_attn_decode<2, kTrace>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((k_attn_decode<4, kTrace>), grid, block, 0, stream, a);
+  } else if (a.G <= 1) {
+    hipLaunchKernelGGL((k_attn_decode_coop<1, W, kTrace>), grid, block, 0, stream, a);
+  } else if (a.G <= 2) {
+    hipLaunchKernelGGL((k_attn_decode_coop<2, W, kTrace>), grid, block, 0, stream, a);
+  } else if (a.G <= 4) {
+    hipLaunchKernelGGL((k_attn_decode_coop<4, W, kTrace>), grid, block, 0, stream, a);
+  } else if (a.G <= 8) {
+    hipLaunchKernelGGL((k_attn_decode_coop<8, W, kTrace>), grid, block, 0, stream, a);
+  } else {
+    hipLaunchKernelGGL((k_attn_decode_coop<16, W, kTrace>), grid, block, 0, stream, a);
+  }
+}
+
+// Waves per work-group (W).  One wave takes about 1.3 us per group (GP = 4)
+// whatever the load, so a launch of few chunks is bound by the chain of groups
+// of its longest one; W waves cut the chain W-fold, at about 2.3 (W = 4) and
+// 3.3 us (W = 8) per step of W groups, since they share the CU's LDS.  A launch
+// that fills the chip anyway is bound by the sum of its work, where W > 1 pays
+// for W prologues and the exchanges.  Measured, us per decoding step (append,
+// decode, merge; int4, 4000 cached tokens in two chunks), W = 1 / 2 / 4 / 8 at
+// GP = 4: 64 chunks 54 / 43 / 31 / 26, 256: 56 / 45 / 34 / 33, 512: 60 / 50 /
+// 40 / 55, 768: 66 / 55 / 49 / 77, 1024: 71 / 62 / 72 / 99, 1536: 85 / 81 / 90 /
+// 143, 2560: 134 / 138 / 145 / 230.  GP = 8 (one wave spills there; it measured
+// 69 at 64 chunks, 78 at 512, 94 at 1024): 64 chunks - / 46 / 33 / 27, 512:
+// - / 56 / 44 / 59, 1024: - / 68 / 78 / 109, and 497 / 389 / 430 / 664 for 8192
+// chunks of 8000 tokens.  Chunks of 48 groups and more spread the prologues over
+// more steps and make the longest chain longer: 1024 chunks of sequences of 256
+// to 16383 tokens (GP = 8) 144 / 92 / 77 / 92, 2048 chunks of 16000 tokens
+// (GP = 16) 365 / 337 / 294 / 352.
+static int decode_waves(const DecodeArgs& a) {
+  const long units = (long)a.B * a.Hkv * a.nsplit;
+  const int len = ceil_div(a.max_groups, a.nsplit);  // groups of the longest chunk, or one more
+  if (units <= 256 && len >= 8) return 8;
+  if (units <= (len >= 48 ? 2048 : 768) && len >= 4) return 4;
+  if (a.G > 4 || (units <= 1792 && len >= 2)) return 2;
+  return 1;
+}
+
 hipError_t launch_attn_decode(const DecodeArgs& a, hipStream_t stream) {
-  const int gp = a.G <= 1 ? 1 : a.G <= 2 ? 2 : a.G <= 4 ? 4 : a.G <= 8 ? 8 : 16;
   // group chunks, then one work-group per (sequence, KV head) for the buffer
   const int total = a.B * a.Hkv * a.nsplit + (a.tk ? a.B * a.Hkv : 0);
+  const int W = decode_waves(a);
   if (a.trace) {
-    switch (gp) {
-      case 1: hipLaunchKernelGGL((k_attn_decode<1, true>), dim3(total), dim3(64), 0, stream, a); break;
-      case 2: hipLaunchKernelGGL((k_attn_decode<2, true>), dim3(total), dim3(64), 0, stream, a); break;
-      case 4: hipLaunchKernelGGL((k_attn_decode<4, true>), dim3(total), dim3(64), 0, stream, a); break;
-      case 8: hipLaunchKernelGGL((k_attn_decode<8, true>), dim3(total), dim3(64), 0, stream, a); break;
-      default: hipLaunchKernelGGL((k_attn_decode<16, true>), dim3(total), dim3(64), 0, stream, a); break;
+    switch (W) {
+      case 1: launch_decode<1, true>(a, total, stream); break;
+      case 2: launch_decode<2, true>(a, total, stream); break;
+      case 4: launch_decode<4, true>(a, total, stream); break;
+      default: launch_decode<8, true>(a, total, stream); break;
     }
   } else {
-    switch (gp) {
-      case 1: hipLaunchKernelGGL((k_attn_decode<1, false>), dim3(total), dim3(64), 0, stream, a); break;
-      case 2: hipLaunchKernelGGL((k_attn_decode<2, false>), dim3(total), dim3(64), 0, stream, a); break;
-      case 4: hipLaunchKernelGGL((k_attn_decode<4, false>), dim3(total), dim3(64), 0, stream, a); break;
-      case 8: hipLaunchKernelGGL((k_attn_decode<8, false>), dim3(total), dim3(64), 0, stream, a); break;
-      default: hipLaunchKernelGGL((k_attn_decode<16, false>), dim3(total), dim3(64), 0, stream, a); break;
+    switch (W) {
+      case 1: launch_decode<1, false>(a, total, stream); break;
+      case 2: launch_decode<2, false>(a, total, stream); break;
+      case 4: launch_decode<4, false>(a, total, stream); break;
+      default: launch_decode<8, false>(a, total, stream); break;
     }
   }
   hipError_t e = hipGetLastError();

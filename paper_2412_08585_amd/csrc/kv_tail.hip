@@ -187,7 +187,8 @@ hipError_t launch_append_kv(const AppendArgs& a, int B, hipStream_t stream) {
 }
 
 // ---- decode of the buffered tokens --------------------------------------
-// One wave per (sequence b, KV head kh) and all G query rows of kh.  The
+// One work-group per (sequence b, KV head kh) and all G query rows of kh, each
+// wave taking every W-th row.  The
 // buffer holds at most 63 tokens, so the integer products run on the VALU
 // (v_dot4): lane t scores token t, then lane L accumulates channels 2L, 2L+1.
 // The result is the buffer's chunk state (m, l, O) in workspace slot
@@ -197,15 +198,15 @@ hipError_t launch_append_kv(const AppendArgs& a, int B, hipStream_t stream) {
 // so it needs no launch of its own and fills the slots the group chunks
 // leave free at the end.
 
-template <int GP, bool kTrace>
+template <int GP, int W, bool kTrace>
 __device__ void decode_tail_body(const DecodeArgs& a, int bx) {
   __shared__ float lut[8];
   __shared__ int q8s[GP][32];        // int8 query codes, 4 per word
   __shared__ float sqs[GP];
   __shared__ int p8s[GP][16];        // Q(P~) codes of the 64 slots, 4 per word
   __shared__ float4 rowv[GP];        // m, l, g = s_P s_V, -
-  const int lane = threadIdx.x;
-  if (lane < 8) lut[lane] = kLut[lane];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (threadIdx.x < 8) lut[lane] = kLut[lane];
   const int b = bx / a.Hkv, kh = bx % a.Hkv;
   const int G = a.G;
   const DecodeSeq sq_ = decode_seq(a, b);
@@ -217,7 +218,7 @@ __device__ void decode_tail_body(const DecodeArgs& a, int bx) {
   const int trow = kTrace && b == a.tr_b && kh == a.tr_h / G && a.tr_g == ng ? a.tr_h % G : -1;
 
   // ---- q -> int8 per query row (Algorithm 2; eq. step1bpq) ----------------
-  for (int r = 0; r < G; ++r) {
+  for (int r = w; r < G; r += W) {
     const unsigned qq = reinterpret_cast<const unsigned*>(a.q)[((long)b * a.Hq + kh * G + r) * 64 + lane];
     const float x0 = (float)__builtin_bit_cast(_Float16, (unsigned short)(qq & 0xffffu));
     const float x1 = (float)__builtin_bit_cast(_Float16, (unsigned short)(qq >> 16));
@@ -248,7 +249,7 @@ __device__ void decode_tail_body(const DecodeArgs& a, int bx) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) kw[i] = krow[i];
     const bool vis = lane < nt;
-    for (int r = 0; r < G; ++r) {
+    for (int r = w; r < G; r += W) {
       int acc = 0;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -287,7 +288,7 @@ __device__ void decode_tail_body(const DecodeArgs& a, int bx) {
       w0[i] = v0[i];
       w1[i] = v1[i];
     }
-    for (int r = 0; r < G; ++r) {
+    for (int r = w; r < G; r += W) {
       int acc0 = 0, acc1 = 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {

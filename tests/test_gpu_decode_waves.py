@@ -1,0 +1,104 @@
+"""Decode with one, two, four and eight waves per chunk: the waves share the
+groups of a chunk, and the result is that of one wave, bit for bit.
+
+The number of waves follows the number of chunks in the launch, so one sequence
+is decoded alone and repeated 160, 500 and 1000 times (two KV heads, one chunk
+each: 2, 320, 1000 and 2000 chunks); its rows must have the same bits each time,
+and the lone one is checked against the CPU oracle.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+SM = 1 / np.sqrt(128)
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+@pytest.fixture(scope="module")
+def ta(dev):
+    import paper_2412_08585_amd as ta
+    ta.lib()
+    return ta
+
+
+def _rand(shape, seed):
+    return torch.randn(*shape, generator=torch.Generator().manual_seed(seed)).half()
+
+
+def _bits(t):
+    return t.contiguous().view(torch.int16 if t.dtype == torch.float16 else torch.int32)
+
+
+# groups: below, at and past the steps of 2, 4 and 8 groups; one group; past the
+# 64 table entries a lane holds at a time (64 steps of 8 groups)
+CASES = [(G, ng) for G in (1, 2, 4, 8, 16) for ng in (1, 9, 31)] + [(3, 16), (5, 22), (2, 515)]
+
+
+@pytest.mark.parametrize("G,ng", CASES)
+def test_decode_waves_give_the_bits_of_one(orc, ta, dev, G, ng):
+    print(f"decode waves G={G} ng={ng}", flush=True)
+    Hkv, bits = 2, [4, 2]
+    Hq = G * Hkv
+    k, v = _rand((1, Hkv, 64 * ng, 128), 10 * ng + G), _rand((1, Hkv, 64 * ng, 128), 11 * ng + G)
+    k[..., 7] *= 10
+    if ng > 20:  # a maximum near the end: factors that cut the earlier groups off
+        k[:, :, 64 * (ng - 3)] *= 4
+    q = _rand((1, Hq, 128), 12 * ng + G)
+    rng = np.random.default_rng(ng)
+    bt = rng.permutation(4 * ng).astype(np.int32)[None]
+    gt = rng.permutation(ng).astype(np.int32)[None]
+    cache = ta.PagedKVCache(4 * ng, ng, bits, dev)
+    btd, gtd, qd = torch.from_numpy(bt).to(dev), torch.from_numpy(gt).to(dev), q.to(dev)
+    ta.turbo_quantize_kv(k.to(dev), v.to(dev), cache, btd, gtd)
+    sl = torch.full((1,), 64 * ng, dtype=torch.int32, device=dev)
+
+    def run(B, bt_, gt_):
+        args = (qd.repeat(B, 1, 1), cache, sl.repeat(B), bt_.repeat(B, 1), gt_.repeat(B, 1))
+        o, lse = ta.turbo_attn_decode(*args, SM, 1000, return_lse=True)
+        o2, lse2 = ta.turbo_attn_decode(*args, SM, 2, return_lse=True)  # chunks of two groups
+        torch.cuda.synchronize()
+        return o, lse, o2, lse2
+
+    alone = run(1, btd, gtd)
+    ref = orc.quantize_kv(k, v, bits)
+    ro, rl = orc.attn_decode(q, ref, [64 * ng], SM, split=ng)
+    err = np.abs(alone[0].float().cpu().numpy() - ro) / np.abs(ro).max(axis=-1, keepdims=True)
+    assert err.max() < 1e-3
+    assert np.abs(alone[1].cpu().numpy() - rl).max() < 1e-4
+    skip = gtd.clone()
+    skip[0, ng // 2] = -1  # a group that is not attended
+    skipped = run(1, btd, skip)
+    for B in (160, 500, 1000):
+        for got, want in zip(run(B, btd, gtd) + run(B, btd, skip), alone + skipped):
+            assert torch.equal(_bits(got), _bits(want).expand(B, *want.shape[1:])), B
+
+
+@pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
+def test_decode_waves_trace_the_same_integers(ta, dev, G):
+    ng, Hkv, bits = 11, 2, [2, 4]
+    k, v = _rand((1, Hkv, 64 * ng, 128), 50 + G), _rand((1, Hkv, 64 * ng, 128), 60 + G)
+    q = _rand((1, G * Hkv, 128), 70 + G).to(dev)
+    bt = torch.arange(4 * ng, dtype=torch.int32, device=dev)[None]
+    gt = torch.arange(ng, dtype=torch.int32, device=dev)[None]
+    cache = ta.PagedKVCache(4 * ng, ng, bits, dev)
+    ta.turbo_quantize_kv(k.to(dev), v.to(dev), cache, bt, gt)
+    sl = torch.full((1,), 64 * ng, dtype=torch.int32, device=dev)
+    for (h, g) in ((0, 0), (G, 6), (2 * G - 1, ng - 1)):
+        want = None
+        for B in (1, 160, 500, 1000):
+            print(f"decode waves trace G={G} B={B} h={h} g={g}", flush=True)
+            _, t = ta.turbo_attn_decode_trace(q.repeat(B, 1, 1), cache, sl.repeat(B),
+                                              bt.repeat(B, 1), gt.repeat(B, 1), (B - 1, h, g), SM,
+                                              1000)
+            want = t if want is None else want
+            assert np.any(t["pvacc"])
+            for name in t:
+                assert np.array_equal(t[name], want[name]), (B, name)
