@@ -544,8 +544,6 @@ int turbo_sas_softmax(const float* x, float* y, int64_t rows, int cols, hipStrea
   a.y = y;
   a.rows = rows;
   a.cols = cols;
-  a.vec = cols % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
-          reinterpret_cast<uintptr_t>(y) % 16 == 0;
   return turbo::launch_sas_softmax(a, stream) == hipSuccess ? TURBO_OK : TURBO_ERR_HIP;
 }
 

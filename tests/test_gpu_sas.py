@@ -68,13 +68,33 @@ def test_sas_softmax_parity(orc, ta, dev, rows, cols, aligned):
     ref = orc.sas_softmax_rows(x.numpy())
     if aligned:
         xd = x.to(dev)
-    else:  # 4-byte offset: the kernel takes its scalar path
+    else:  # 4-byte offset: rows that start inside a 16-byte unit
         buf = torch.empty(rows * cols + 1, dtype=torch.float32, device=dev)
         xd = buf[1:].view(rows, cols)
         xd.copy_(x)
     y = ta.turbo_sas_softmax(xd)
     torch.cuda.synchronize()
     _check(y, ref, f"rows={rows} cols={cols}")
+
+
+@pytest.mark.parametrize("cols", [1, 2, 3, 5, 253, 254, 257, 509, 1021, 1022, 2045, 2047, 4093, 4095,
+                                  8189, 16381, 16383, 17405, 17407])
+@pytest.mark.parametrize("xo,yo", [(0, 0), (1, 1), (3, 3), (0, 2), (2, 1)])
+def test_sas_softmax_rows_that_start_anywhere(orc, ta, dev, cols, xo, yo):
+    """Ragged rows (each starts 0 to 3 values into a 16-byte unit), with input
+    and output lying alike or not, at the edges of the register sizes; nothing
+    around the output is written."""
+    rows = 6
+    _log(f"sas_softmax rows={rows} cols={cols} x offset={xo} y offset={yo}")
+    x = _scores(rows, cols, cols * 8 + xo)
+    xb = torch.full((rows * cols + 8,), float("nan"), device=dev)
+    yb = torch.full((rows * cols + 8,), -7.0, device=dev)
+    xd, yd = (b[o:o + rows * cols].view(rows, cols) for b, o in ((xb, xo), (yb, yo)))
+    xd.copy_(x)
+    ta.turbo_sas_softmax(xd, out=yd)
+    torch.cuda.synchronize()
+    _check(yd, orc.sas_softmax_rows(x.numpy()), f"cols={cols}")
+    assert bool((yb[:yo] == -7.0).all()) and bool((yb[yo + rows * cols:] == -7.0).all())
 
 
 def test_sas_softmax_in_place_and_single_survivor(orc, ta, dev):
