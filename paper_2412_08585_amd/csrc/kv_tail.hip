@@ -30,65 +30,78 @@ struct TailInitArgs {
   float* tscale;            // [batch][Hkv][2]
 };
 
-__global__ __launch_bounds__(256) void k_tail_init(TailInitArgs a) {
-  __shared__ float red[4];
-  const long u = blockIdx.x;  // b * Hkv + h
-  const int tid = threadIdx.x;
-  float mk = 0.0f, mv = 0.0f;
-  for (int j = tid; j < a.nb; j += 256) {
-    mk = fmaxf(mk, a.sk[u * a.nb + j]);
-    mv = fmaxf(mv, a.sv[u * a.nb + j]);
-  }
-  mk = block_max(mk, red);
-  mv = block_max(mv, red);
-  if (tid == 0) {
-    a.tscale[2 * u] = mk;
-    a.tscale[2 * u + 1] = mv;
-  }
-  const int ng = a.N / 64, nt = a.N - 64 * ng;
-  const float ik = univ_inv(mk), iv = univ_inv(mv);
-  const unsigned short* kr = a.k + (u * a.N + 64L * ng) * 128;
-  const unsigned short* vr = a.v + (u * a.N + 64L * ng) * 128;
-  {
-    // K, token-major: thread (t = tid>>2, chunk = tid&3) codes 32 channels
-    const int t = tid >> 2, c0 = 32 * (tid & 3);
-    unsigned w[8];
+// Four 16-byte runs (32 channels) of token row t, zero from row nt on.
+__device__ __forceinline__ void tail_load(const unsigned short* rows, int t, int nt, int c0,
+                                          uint4 (&raw)[4]) {
+  // k and v may lie at any fp16 boundary
+  typedef unsigned u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+  const u32x4_any* src = reinterpret_cast<const u32x4_any*>(rows + t * 128 + c0);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int q[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int c = c0 + 4 * i + e;
-        q[e] = t < nt ? quant_univ((float)__builtin_bit_cast(_Float16, kr[t * 128 + c]), ik) : 0;
-      }
-      w[i] = pack4(q[0], q[1], q[2], q[3]);
-    }
-    uint4* dst = reinterpret_cast<uint4*>(a.tk + (u * 64 + t) * 128 + c0);
-    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
-  }
-  {
-    // V, channel-major: thread (c = tid>>1, hh = tid&1) codes tokens 32hh..+31
-    const int c = tid >> 1, t0 = 32 * (tid & 1);
-    unsigned w[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int q[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int t = t0 + 4 * i + e;
-        q[e] = t < nt ? quant_univ((float)__builtin_bit_cast(_Float16, vr[t * 128 + c]), iv) : 0;
-      }
-      w[i] = pack4(q[0], q[1], q[2], q[3]);
-    }
-    uint4* dst = reinterpret_cast<uint4*>(a.tv + (u * 128 + c) * 64 + t0);
-    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+  for (int i = 0; i < 4; ++i) {
+    raw[i] = make_uint4(0, 0, 0, 0);
+    if (t < nt) raw[i] = make_uint4(src[i].x, src[i].y, src[i].z, src[i].w);
   }
 }
 
+// Their universal-scale codes, four to a word.
+__device__ __forceinline__ void tail_codes(const uint4 (&raw)[4], float inv, unsigned (&w)[8]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f16x8_t h = __builtin_bit_cast(f16x8_t, raw[i]);
+    int q[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = quant_univ((float)h[e], inv);
+    w[2 * i] = pack4(q[0], q[1], q[2], q[3]);
+    w[2 * i + 1] = pack4(q[4], q[5], q[6], q[7]);
+  }
+}
+
+// One work-group per (sequence, KV head) and tensor (even: K, odd: V).  A few
+// KB per work-group: bound by latency, so the token rows are loaded in 16-byte
+// runs, ahead of the reduction of the block scales, and V is transposed through
+// LDS: 20 sequence-heads of 1001 tokens 4.9 us, against 23.6 us with 2-byte
+// loads and K and V in one work-group.
+__global__ __launch_bounds__(256) void k_tail_init(TailInitArgs a) {
+  __shared__ float red[4];
+  __shared__ int8_t tile[64 * kTileStride];
+  const long u = blockIdx.x >> 1;  // b * Hkv + h
+  const bool isv = blockIdx.x & 1;
+  const int tid = threadIdx.x;
+  const int ng = a.N / 64, nt = a.N - 64 * ng;
+  const int t = tid >> 2, c0 = 32 * (tid & 3);
+  uint4 raw[4];
+  tail_load((isv ? a.v : a.k) + (u * a.N + 64L * ng) * 128, t, nt, c0, raw);
+  const float* sb = (isv ? a.sv : a.sk) + u * a.nb;
+  float m = 0.0f;
+  for (int j = tid; j < a.nb; j += 256) m = fmaxf(m, sb[j]);
+  m = block_max(m, red);
+  if (tid == 0) a.tscale[2 * u + isv] = m;
+  unsigned w[8];
+  tail_codes(raw, univ_inv(m), w);
+  if (!isv) {  // token-major
+    uint4* dst = reinterpret_cast<uint4*>(a.tk + (u * 64 + t) * 128 + c0);
+    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    *reinterpret_cast<uint2*>(tile + t * kTileStride + c0 + 8 * i) = make_uint2(w[2 * i], w[2 * i + 1]);
+  __syncthreads();
+  // channel-major: thread (c = tid>>1, hh = tid&1) writes tokens 32hh .. +31
+  const int c = tid >> 1, r0 = 32 * (tid & 1);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int8_t* p = tile + (r0 + 4 * i) * kTileStride + c;
+    w[i] = pack4(p[0], p[kTileStride], p[2 * kTileStride], p[3 * kTileStride]);
+  }
+  uint4* dst = reinterpret_cast<uint4*>(a.tv + (u * 128 + c) * 64 + r0);
+  dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+  dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+}
+
 hipError_t launch_tail_init(const TailInitArgs& a, int B, hipStream_t stream) {
-  hipLaunchKernelGGL(k_tail_init, dim3(B * a.Hkv), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(k_tail_init, dim3(2 * B * a.Hkv), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -3,8 +3,12 @@
 // eq. step2bpq) with the cache writes of Algorithm 1.
 //
 // One workgroup of 256 threads handles one (sequence b, KV head h, 64-token
-// block j) for both K and V.  The int8 block is staged token-major in LDS;
-// step 2 then works channel by channel out of LDS.  k_quantize_kv_blocks is
+// block j) of K (even) or V (odd).  The int8 block is staged token-major in LDS;
+// step 2 then works channel by channel out of LDS.  Large inputs are bound by HBM
+// (Phi-3-medium 4 x 4096: 33.8 us, 4.8 TB/s, the rate of a plain copy), small
+// ones by the latency of one block, which is why K and V, done one after the
+// other at first, go to workgroups of their own: 4 heads x 512 tokens 7.5 -> 5.3
+// us, Phi-3-medium 34.8 -> 33.8 us.  k_quantize_kv_blocks is
 // step 1 alone with blocks of 32 or 128 tokens (the B_c variants of Table 3);
 // it keeps the 64-token storage layouts and writes no cache.
 #include "turbo_common.h"
@@ -93,7 +97,8 @@ __global__ __launch_bounds__(kQkvThreads) void k_quantize_kv(QuantArgs a) {
   __shared__ uint8_t ctile[64 * kTileStride];  // K codes, token-major
   __shared__ float red[4];
 
-  const int j = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int j = blockIdx.x >> 1, h = blockIdx.y, b = blockIdx.z;
+  const bool isv = blockIdx.x & 1;  // work-group uniform
   const int tid = threadIdx.x;
   const long unit = (long)b * a.Hkv + h;
   const int r0 = j * 64;
@@ -117,20 +122,17 @@ __global__ __launch_bounds__(kQkvThreads) void k_quantize_kv(QuantArgs a) {
   const int bits = ((a.int2_mask >> h) & 1ull) ? 2 : 4;
   const int head_off = 512 * (4 * h - 2 * __popcll(a.int2_mask & ((1ull << h) - 1ull)));
   int8_t* meta = a.gmeta + (slot * a.Hkv + h) * 512;
+  float* gscale = a.gscale + (slot * a.Hkv + h) * 2;
 
-  // ---- K ----
-  float s = quant_block<4>(a.k + xoff, nr, tile, red, a.k8 + (unit * a.nb + j) * 8192);
-  if (tid == 0) a.sk[unit * a.nb + j] = s;
+  const float s = quant_block<4>((isv ? a.v : a.k) + xoff, nr, tile, red,
+                                 isv ? nullptr : a.k8 + (unit * a.nb + j) * 8192);
+  if (tid == 0) (isv ? a.sv : a.sk)[unit * a.nb + j] = s;
   __syncthreads();
-  if (do_cache)
-    compress_k(tile, ctile, bits, meta, a.gscale + (slot * a.Hkv + h) * 2 + 0, s, page, a.pages,
-               a.page_bytes, head_off);
-  __syncthreads();
-
-  // ---- V ----
-  s = quant_block<4>(a.v + xoff, nr, tile, red, nullptr);
-  if (tid == 0) a.sv[unit * a.nb + j] = s;
-  __syncthreads();
+  if (!isv) {
+    if (do_cache)
+      compress_k(tile, ctile, bits, meta, gscale, s, page, a.pages, a.page_bytes, head_off);
+    return;
+  }
   {
     // channel-major int8 block: thread (c = tid>>1, hh) writes 32 tokens
     const int c = tid >> 1, hh = tid & 1;
@@ -146,8 +148,7 @@ __global__ __launch_bounds__(kQkvThreads) void k_quantize_kv(QuantArgs a) {
     dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
   }
   if (do_cache)
-    compress_v(tile, bits, meta, a.gscale + (slot * a.Hkv + h) * 2 + 1, s, page, a.pages,
-               a.page_bytes, head_off);
+    compress_v(tile, bits, meta, gscale + 1, s, page, a.pages, a.page_bytes, head_off);
 }
 
 // Step 1 with BC-token blocks (BC = 32 or 128): one workgroup per (b, h,
@@ -200,7 +201,7 @@ hipError_t launch_quantize_kv(const QuantArgs& a, int B, hipStream_t stream) {
     hipLaunchKernelGGL(k_quantize_kv_blocks<128>, dim3((a.nb + 1) / 2, a.Hkv, B),
                        dim3(kQkvThreads), 0, stream, a);
   } else {
-    hipLaunchKernelGGL(k_quantize_kv, dim3(a.nb, a.Hkv, B), dim3(kQkvThreads), 0, stream, a);
+    hipLaunchKernelGGL(k_quantize_kv, dim3(2 * a.nb, a.Hkv, B), dim3(kQkvThreads), 0, stream, a);
   }
   return hipGetLastError();
 }
