@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void k_append_kv(AppendArgs a) {
   }
   __syncthreads();
   compress_k(tile, ctile, bits, meta, a.gscale + (slot * a.Hkv + h) * 2 + 0, sK, page, a.pages,
-             a.page_bytes, head_off);
+             a.page_bytes, head_off, tid);
   __syncthreads();
   // V buffer (channel-major in memory) into the token-major tile
   {
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void k_append_kv(AppendArgs a) {
   }
   __syncthreads();
   compress_v(tile, bits, meta, a.gscale + (slot * a.Hkv + h) * 2 + 1, sV, page, a.pages,
-             a.page_bytes, head_off);
+             a.page_bytes, head_off, tid);
 }
 
 hipError_t launch_append_kv(const AppendArgs& a, int B, hipStream_t stream) {

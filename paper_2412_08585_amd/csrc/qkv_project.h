@@ -11,7 +11,7 @@ namespace turbo {
 struct QkvArgs {
   const void* x;   // fp16 [B][N][D]
   const void* w;   // fp16 [F][D], F = (Hq + 2 Hkv) * 128
-  int B, N, D, Hq, Hkv, nb, ntile;
+  int B, N, D, Hq, Hkv, nb;
   int8_t* q8;      // [B][Hq][nb*64][128]
   float* sq;       // [B][Hq][nb]
   int8_t* k8;      // [B][Hkv][nb*64][128]
@@ -31,7 +31,7 @@ struct QkvArgs {
   _Float16* y;     // test hook: the fp16 projection [B][N][F] (null: not written)
 };
 
-// Tokens per work-group tile (ntile = ceil(N / kQkvTileTokens)).
+// Tokens of the larger work-group tile.
 constexpr int kQkvTileTokens = 256;
 
 hipError_t launch_qkv_project(const QkvArgs& a, hipStream_t stream);

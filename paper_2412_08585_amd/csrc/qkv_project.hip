@@ -14,20 +14,25 @@
 // same LDS-tile routines as k_quantize_kv.  Q, K and V never reach HBM in
 // fp16.
 //
-// Tiling.  A work-group of four waves computes a 256-token x 256-feature tile
-// (two heads).  The contraction runs in stages of 32 columns: the tile's 256
-// X rows and 256 W rows of a stage (64 bytes each, 16-byte chunks swizzled
-// by row so that the operand reads are free of bank conflicts) are loaded
-// straight into LDS by buffer loads, into a ring of four stage buffers, four
-// stages ahead.  Each wave reads the next stage's operands into registers
-// while the current stage's MFMAs run, and issues its part of the loads
-// spread between those MFMAs; one barrier per stage.  Wave (wm, wn) owns
-// tokens 128 wm .. +127 and head wn of the pair: 4 x 4 MFMA blocks of
-// 32 x 32, 256 fp32 accumulators per lane, which live in the AGPR file (one
-// wave per SIMD; this file is built as a translation unit of its own,
-// without the VGPR-only MFMA form of the attention kernels).  Every operand
-// byte leaves L2 once per work-group: X is read once per head pair and W
-// once per 256-token tile.
+// Tiling.  A work-group of kWM x kWN waves computes a tile of 32 kMB kWM tokens
+// by 32 kNB kWN features, wave (wm, wn) its kMB x kNB MFMA blocks of 32 x 32.
+// The contraction runs in stages of 64 columns: the tile's X and W rows of a
+// stage (128 bytes each, 16-byte chunks swizzled by row so that the operand
+// reads are free of bank conflicts) are loaded straight into LDS by buffer
+// loads, into two stage buffers used in turn.  A wave reads the operands of the
+// next 16 columns into registers while the current ones' MFMAs run; the barrier
+// of a stage lies before its last 16 columns, whose MFMAs cover the first reads
+// of the next stage and the issue of the loads of the one after.
+//   * 256 tokens x 256 features (two heads), 2 x 4 waves of 4 x 2 blocks: two
+//     waves per SIMD, so that one's MFMAs fill the other's waits.
+//     Bound by LDS as much as by the MFMAs: per 64 columns and CU, operand
+//     reads of 192 KB and the staged 64 KB at 128 bytes a clock are as many
+//     clocks as the MFMAs' 2048.  Phi-3-medium 4 x 4096 tokens, D = 5120:
+//     1.10-1.17 ms, against 1.24-1.25 (four waves of 4 x 4 blocks, one per SIMD,
+//     stages of 32 columns); without the epilogue 1.10 against 1.17.
+//   * 128 tokens x 128 features (one head), 2 x 2 waves of 2 x 2 blocks, two
+//     work-groups per CU: for inputs whose large tiles would leave CUs idle
+//     (777 tokens, D = 4096, 48 heads: 57 us against 91).
 #include "turbo_common.h"
 #include "quant_tiles.h"
 #include "qkv_project.h"
@@ -37,12 +42,26 @@ namespace turbo {
 typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kProjThreads = 256;
-constexpr int kPRow = 64;                // LDS bytes per staged row: 32 fp16 columns
-constexpr int kPOp = 256 * kPRow;        // one operand (256 rows) of one stage
-constexpr int kPStage = 2 * kPOp;        // X rows, then W rows
+constexpr int kPRow = 128;                  // LDS bytes per staged row: 64 fp16 columns
 constexpr int kEpiTile = 64 * kTileStride;  // one 64 x 128 int8 block (k_quantize_kv layout)
-static_assert(3 * kEpiTile <= kPStage, "three epilogue tiles fit in a stage");
+
+template <int kWM_, int kWN_, int kMB_, int kNB_>
+struct QkvTile {
+  static constexpr int kWM = kWM_, kWN = kWN_, kMB = kMB_, kNB = kNB_;
+  static constexpr int kWaves = kWM * kWN, kThreads = 64 * kWaves;
+  static constexpr int kTok = 32 * kMB * kWM, kFeat = 32 * kNB * kWN;
+  static constexpr int kHeads = kFeat / 128, kBlocks = kTok / 64;  // FlashQ blocks: kBlocks a head
+  static constexpr int kXBytes = kTok * kPRow, kStage = (kTok + kFeat) * kPRow;
+  static constexpr int kLoads = kStage / 1024 / kWaves;  // 1 KiB loads per wave and stage
+  static constexpr int kTeams = kThreads / 256;          // step 2 runs on 256 threads each
+  static constexpr int kTiles = kHeads * kBlocks;        // FlashQ blocks of the work-group
+  static_assert(kNB == 2 && kMB % 2 == 0, "a wave covers half a head and whole FlashQ blocks");
+  static_assert(kXBytes / 1024 % kWaves == 0 && kFeat * kPRow / 1024 % kWaves == 0, "even loads");
+  static_assert((kTiles + kTeams) * kEpiTile <= 2 * kStage, "the epilogue's tiles fit");
+  static_assert(kBlocks % kTeams == 0 && kWaves % kTiles == 0, "even epilogue");
+};
+using QkvLarge = QkvTile<2, 4, 4, 2>;
+using QkvSmall = QkvTile<2, 2, 2, 2>;
 
 __device__ __forceinline__ f32x16_t mfma_f16(uint4 a, uint4 b, f32x16_t c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8_t, a),
@@ -96,298 +115,316 @@ __device__ __forceinline__ void qkv_tile(int x, int ntiles, int npairs, int& til
 
 // kY = true only for the test hook that also stores the fp16 projection
 // (the production instance carries no such store).
-template <bool kY>
-__global__ __launch_bounds__(kProjThreads, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void
-k_qkv_project(QkvArgs a) {
-  // four stages, each its own array: the compiler then sees that the loads
-  // into one stage and the operand reads of another do not overlap
-  __shared__ __align__(16) uint8_t st0[kPStage], st1[kPStage], st2[kPStage], st3[kPStage];
-  __shared__ float sblk[8];
+template <typename T, bool kY>
+__global__ __launch_bounds__(T::kThreads, 2) void k_qkv_project(QkvArgs a) {
+  constexpr int kMB = T::kMB, kNB = T::kNB, kWN = T::kWN;
+  __shared__ __align__(16) uint8_t st[2 * T::kStage];
+  __shared__ float part[T::kHeads][T::kBlocks][2];  // maxima of the two half heads
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wv & 1, wn = wv >> 1;
+  const int wm = wv / kWN, wn = wv % kWN;
   const int m = lane & 31, hh = lane >> 5;
   const int nheads = a.Hq + 2 * a.Hkv;
-  const int npairs = ceil_div(nheads, 2);
+  const int nunits = ceil_div(nheads, T::kHeads);
+  const int ntile = ceil_div(a.N, T::kTok);
   const int F = 128 * nheads;
-  int tile, pair;
-  qkv_tile(blockIdx.x, a.B * a.ntile, npairs, tile, pair);
-  const int b = tile / a.ntile;
-  const int t0 = (tile % a.ntile) * kQkvTileTokens;
+  int tile, unit_;
+  qkv_tile(blockIdx.x, a.B * ntile, nunits, tile, unit_);
+  const int head0 = T::kHeads * unit_;
+  const int b = tile / ntile;
+  const int t0 = (tile % ntile) * T::kTok;
 
-  // ---- staging: buffer loads straight into LDS, four stages of 32 columns ----
-  // chunk c of staged row r sits at chunk position c ^ ((r >> 2) & 3).  Per
-  // stage a wave issues 4 X and 4 W loads; load i of wave w fills rows
-  // 16 (4 w + i) .. +15 (1 KiB): lane L takes row + (L >> 2), position L & 3,
-  // i.e. source chunk (L & 3) ^ ((L >> 4) & 3).
+  // ---- staging: buffer loads straight into LDS --------------------------------
+  // chunk c of staged row r sits at chunk position c ^ g(r), g = (r & 7) ^ ((r >> 3) & 1):
+  // any 8 rows from a multiple of 8 and any 16 from a multiple of 16 put one
+  // chunk into distinct 16-byte slots of 32 (64) banks.  Load i of a wave fills
+  // rows 8 j .. + 7 (j = kWaves i + wave; 1 KiB): lane L takes row + (L >> 3),
+  // position L & 7, i.e. source chunk (L & 7) ^ (L >> 3) ^ (j & 1).
   const unsigned D2 = 2u * (unsigned)a.D;  // bytes per row
-  const unsigned vo = (unsigned)(lane >> 2) * D2 + 16u * (unsigned)((lane & 3) ^ ((lane >> 4) & 3));
-  const unsigned xs0 = (unsigned)t0 * D2, ws0 = (unsigned)(256 * pair) * D2;
+  const unsigned vrow = (unsigned)(lane >> 3) * D2;
+  const unsigned vch = (unsigned)((lane & 7) ^ (lane >> 3));
+  // the parity of j is that of the wave (kWaves is even)
+  const unsigned vo = vrow + 16u * (vch ^ (unsigned)(wv & 1));
+  const unsigned xs0 = (unsigned)t0 * D2, ws0 = (unsigned)(128 * head0) * D2;
+  const i32x4 xr = rows_words(static_cast<const _Float16*>(a.x) + (long)b * a.N * a.D, a.N * (int)D2);
+  const i32x4 wr = rows_words(a.w, F * (int)D2);
   // The loads are written as inline assembly: the compiler then neither
   // waits for them before every LDS read nor counts them in its own waits
   // (no other vector-memory operation is in flight during the loop).
-  const i32x4 xr = rows_words(static_cast<const _Float16*>(a.x) + (long)b * a.N * a.D, a.N * (int)D2);
-  const i32x4 wr = rows_words(a.w, F * (int)D2);
-  // load j (0..7) of this wave's part of a stage: X rows (j even) or W rows
-  // (j odd) 16 (4 w + j / 2) .. +15
-  auto dma_j = [&](uint8_t* st, int kk, int j) {
-    const unsigned kb = 64u * (unsigned)kk;  // 32 fp16 columns per stage
-    const int r0 = 16 * (4 * wv + (j >> 1));
-    if (j & 1)
-      lds_load16(wr, vo, ws0 + (unsigned)r0 * D2 + kb, st + kPOp + r0 * kPRow);
-    else
-      lds_load16(xr, vo, xs0 + (unsigned)r0 * D2 + kb, st + r0 * kPRow);
+  constexpr int kXLoads = T::kXBytes / 1024 / T::kWaves;
+  auto dma_j = [&](int buf, int kk, int i) {
+    const unsigned kb = 128u * (unsigned)kk;  // 64 fp16 columns per stage
+    uint8_t* dst = st + buf * T::kStage;
+    if (i < kXLoads) {
+      const int r0 = 8 * (T::kWaves * i + wv);
+      lds_load16(xr, vo, xs0 + (unsigned)r0 * D2 + kb, dst + r0 * kPRow);
+    } else {
+      const int r0 = 8 * (T::kWaves * (i - kXLoads) + wv);
+      lds_load16(wr, vo, ws0 + (unsigned)r0 * D2 + kb, dst + T::kXBytes + r0 * kPRow);
+    }
   };
-  auto dma = [&](uint8_t* st, int kk) {
+  f32x16_t acc[kMB][kNB];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) dma_j(st, kk, j);
-  };
-  f32x16_t acc[4][4];
+  for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = f32x16_t{};
+    for (int nb = 0; nb < kNB; ++nb) acc[mb][nb] = f32x16_t{};
 
-  // operand reads: row 128 wm + 32 mb + m (A) / 128 wn + 32 nb + m (B);
+  // operand reads: row 32 kMB wm + 32 mb + m (A) / 32 kNB wn + 32 nb + m (B);
   // contraction slot (step s, half hh, element e) = column 16 s + 8 hh + e,
-  // chunk 2 s + hh at position (2 s + hh) ^ ((m >> 2) & 3)
-  const int sw = (m >> 2) & 3;
-  const int ao0 = m * kPRow + 16 * ((0 + hh) ^ sw), ao1 = m * kPRow + 16 * ((2 + hh) ^ sw);
-  const int aA = 128 * wm * kPRow, aB = kPOp + 128 * wn * kPRow;
-  // operands of one stage in registers: [k-step][block]
-  typedef uint4 StageOps[2][4];
-  auto read_stage = [&](const uint8_t* st, StageOps& A, StageOps& Bo) {
-    const uint8_t* sa = st + aA;
-    const uint8_t* sb = st + aB;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      A[0][i] = *reinterpret_cast<const uint4*>(sa + ao0 + i * 32 * kPRow);
-      Bo[0][i] = *reinterpret_cast<const uint4*>(sb + ao0 + i * 32 * kPRow);
-      A[1][i] = *reinterpret_cast<const uint4*>(sa + ao1 + i * 32 * kPRow);
-      Bo[1][i] = *reinterpret_cast<const uint4*>(sb + ao1 + i * 32 * kPRow);
-    }
+  // chunk 2 s + hh
+  const int sw = hh ^ (m & 7) ^ ((m >> 3) & 1);
+  const int aA = (32 * kMB * wm + m) * kPRow, aB = T::kXBytes + (32 * kNB * wn + m) * kPRow;
+  struct Ops {
+    uint4 a[kMB], b[kNB];
   };
-  auto mma = [&](const StageOps& A, const StageOps& Bo, int s) {
+  auto read = [&](int buf, int s, Ops& o) {
+    const uint8_t* p = st + buf * T::kStage + 16 * (sw ^ (2 * s));
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int i = 0; i < kNB; ++i) o.b[i] = *reinterpret_cast<const uint4*>(p + aB + 32 * kPRow * i);
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mfma_f16(A[s][mb], Bo[s][nb], acc[mb][nb]);
+    for (int i = 0; i < kMB; ++i) o.a[i] = *reinterpret_cast<const uint4*>(p + aA + 32 * kPRow * i);
   };
-  const int nk = a.D / 32;
-  // The loads write LDS behind the compiler's back: their completion is
-  // waited for by hand (a wave's loads complete in order, eight per stage),
-  // and a plain s_barrier then covers the other waves' parts (__syncthreads
-  // would also wait for the loads still in flight).  Step k runs stage k's
-  // MFMAs from registers, reads stage k + 1 into the other register set and
-  // loads stage k + 4 into the slot of stage k; its closing barrier makes
-  // stage k + 2 visible (16 loads, stages k + 3 and k + 4, may still be in
-  // flight) and tells that every wave has read stage k + 1.  Past the end
-  // the last stage is loaded again, so that every step issues the same
-  // number of loads.
-  StageOps A0, B0, A1, B1;
-  dma(st0, 0);
-  dma(st1, min(1, nk - 1));
-  dma(st2, min(2, nk - 1));
-  dma(st3, min(3, nk - 1));
-  asm volatile("s_waitcnt vmcnt(24)\n\ts_barrier" ::: "memory");
-  read_stage(st0, A0, B0);
-  __builtin_amdgcn_s_waitcnt(0xC07F);
-  asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
-  // step k: the slot of stage k (in registers since step k - 1, and every
-  // wave has passed the barrier after that read) takes stage k + 4
-  auto step = [&](uint8_t* slot_k, const uint8_t* slot_k1, StageOps& Ak, StageOps& Bk,
-                  StageOps& An, StageOps& Bn, int k) {
-    // the stage's 32 MFMAs in eight groups of four, each followed by one
-    // load of stage k + 4 and two operand reads of stage k + 1
-    const uint8_t* sa = slot_k1 + aA;
-    const uint8_t* sb = slot_k1 + aB;
-    const int kn = min(k + 4, nk - 1);
+  auto mma = [&](const Ops& o) {
 #pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const int s_ = g >> 2, q = g & 3;
+    for (int mb = 0; mb < kMB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb) acc[q][nb] = mfma_f16(Ak[s_][q], Bk[s_][nb], acc[q][nb]);
-      __builtin_amdgcn_sched_barrier(0);
-      dma_j(slot_k, kn, g);
-      // reads: group g fetches block (g >> 1) of k-step (g & 1), A and B
-      const int rb = g >> 1, rs = g & 1;
-      An[rs][rb] = *reinterpret_cast<const uint4*>(sa + (rs ? ao1 : ao0) + rb * 32 * kPRow);
-      Bn[rs][rb] = *reinterpret_cast<const uint4*>(sb + (rs ? ao1 : ao0) + rb * 32 * kPRow);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // lgkmcnt(0) through the builtin, so that the compiler knows the operand
-    // reads have landed; vmcnt(16) for the hidden loads by hand
+      for (int nb = 0; nb < kNB; ++nb) acc[mb][nb] = mfma_f16(o.a[mb], o.b[nb], acc[mb][nb]);
+  };
+  const int nk = a.D / 64;
+  Ops o0, o1;
+#pragma unroll
+  for (int i = 0; i < T::kLoads; ++i) dma_j(0, 0, i);
+  if (nk > 1) {
+#pragma unroll
+    for (int i = 0; i < T::kLoads; ++i) dma_j(1, 1, i);
+    static_assert(T::kLoads == 8, "the wait leaves the second stage's loads in flight");
+    asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  }
+  read(0, 0, o0);
+  // Stage k in buffer buf.  Its loads were issued a stage ago, and its first
+  // operands read behind the last MFMAs of stage k - 1.
+  auto stage = [&](auto bufc, int k) {
+    constexpr int buf = decltype(bufc)::value;
+    read(buf, 1, o1);
+    mma(o0);
+    __builtin_amdgcn_sched_barrier(0);
+    read(buf, 2, o0);
+    mma(o1);
+    __builtin_amdgcn_sched_barrier(0);
+    read(buf, 3, o1);
+    mma(o0);
+    // every operand of the stage is in registers (lgkmcnt(0), through the builtin
+    // so that the compiler knows), and the wave's loads of stage k + 1 have
+    // landed; behind the barrier that holds for every wave, so the buffer is
+    // free and the other one complete
     __builtin_amdgcn_s_waitcnt(0xC07F);
-    asm volatile("s_waitcnt vmcnt(16)\n\ts_barrier" ::: "memory");
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    // past the end the last stage is loaded and read again: no branch
+    read(buf ^ 1, 0, o0);
+    const int kn = min(k + 2, nk - 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int mb = 0; mb < kMB; ++mb) {
+#pragma unroll
+      for (int nb = 0; nb < kNB; ++nb) acc[mb][nb] = mfma_f16(o1.a[mb], o1.b[nb], acc[mb][nb]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < T::kLoads / kMB; ++i) dma_j(buf, kn, T::kLoads / kMB * mb + i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
-  for (int k = 0; k < nk; k += 4) {
-    step(st0, st1, A0, B0, A1, B1, k);
-    if (k + 1 < nk) step(st1, st2, A1, B1, A0, B0, k + 1);
-    if (k + 2 < nk) step(st2, st3, A0, B0, A1, B1, k + 2);
-    if (k + 3 < nk) step(st3, st0, A1, B1, A0, B0, k + 3);
+  for (int k = 0; k < nk; k += 2) {
+    stage(std::integral_constant<int, 0>{}, k);
+    if (k + 1 < nk) stage(std::integral_constant<int, 1>{}, k + 1);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
   // ---- epilogue: fp16 outputs, FlashQ step 1 per 64-token block --------------
-  // lane (m, hh), register r of (mb, nb) <-> token 128 wm + 32 mb + 8 (r/4) +
-  // 4 hh + r%4 of the tile, channel 32 nb + m of head 2 pair + wn; FlashQ
-  // block i = mb >> 1 of the wave is block 2 wm + i of the tile
-  const int head = 2 * pair + wn;
+  // lane (m, hh), register r of (mb, nb) <-> token 32 (kMB wm + mb) + 8 (r/4) +
+  // 4 hh + r%4 of the tile, channel 64 (wn & 1) + 32 nb + m of head wn / 2
+  // (of the tile); FlashQ block kMB / 2 wm + (mb >> 1)
+  const int hl = wn >> 1, half = wn & 1;
+  const int head = head0 + hl;
   const bool hv = head < nheads;  // wave-uniform (an odd head count leaves one out)
-  // epilogue tile t (0..8) in stage t / 3, slot t % 3
-  auto etile = [&](int t) -> uint8_t* {
-    uint8_t* st = t < 3 ? st0 : (t < 6 ? st1 : st2);
-    return st + (t % 3) * kEpiTile;
-  };
-  // one block at a time (128 accumulators of a lane), which bounds the
-  // registers the AGPR -> VGPR copies take; the stages are free for the tiles
-  // since the loop's last barrier
-  float sc_[2];
-  // block i of the wave: kFull when all its 64 tokens are below N (the
-  // common case: no per-element masking), else rows nv.. are masked out
-  auto block = [&](auto ic, auto fullc) {
-    constexpr int i = decltype(ic)::value;
-    constexpr bool kFull = decltype(fullc)::value;
-    const int nv = a.N - (t0 + 128 * wm + 64 * i);  // valid rows of the block
-    // max |fp16(y)| = fp16(max |y|): rounding is monotone and symmetric, so
-    // the first pass needs no conversion
+  auto etile = [&](int t) -> uint8_t* { return st + t * kEpiTile; };
+  const int nv0 = a.N - (t0 + 32 * kMB * wm);  // valid rows from the wave's first
+  // max |fp16(y)| = fp16(max |y|): rounding is monotone and symmetric, so
+  // the first pass needs no conversion.  Rows past N hold zeros (their X rows
+  // were read as zeros).
+#pragma unroll
+  for (int i = 0; i < kMB / 2; ++i) {
     float amax = 0.0f;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb)
+      for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = 32 * mi + 8 * (r >> 2) + 4 * hh + (r & 3);
-          amax = fmaxf(amax, (kFull || row < nv) ? fabsf(acc[2 * i + mi][nb][r]) : 0.0f);
+          amax = fmaxf(amax, fabsf(acc[2 * i + mi][nb][r]));
           if constexpr (kY) {
-            if (hv && (kFull || row < nv))
-              a.y[((long)b * a.N + t0 + 128 * wm + 64 * i + row) * (long)F + 128 * head + 32 * nb +
-                  m] = (_Float16)acc[2 * i + mi][nb][r];
+            const int row = 64 * i + 32 * mi + 8 * (r >> 2) + 4 * hh + (r & 3);
+            if (hv && row < nv0)
+              a.y[((long)b * a.N + t0 + 32 * kMB * wm + row) * (long)F + 128 * head + 64 * half +
+                  32 * nb + m] = (_Float16)acc[2 * i + mi][nb][r];
           }
         }
-    amax = (float)(_Float16)amax;
-    amax = wave_max_fast(amax);
-    float inv = 0.0f;
-    sc_[i] = 0.0f;
-    if (amax > 0.0f) {
-      sc_[i] = amax / kQmax;
-      inv = kQmax / amax;
-    }
-    int8_t* tw = reinterpret_cast<int8_t*>(etile(4 * wn + 2 * wm + i));
+    amax = wave_max_fast((float)(_Float16)amax);
+    if (lane == 0) part[hl][kMB / 2 * wm + i][half] = amax;
+  }
+  __syncthreads();
+  // (i a compile-time constant: acc is indexed with it; kFull: all 64 tokens lie
+  // below N, the common case, and no row is masked out)
+  auto codes = [&](auto ic, auto fullc) {
+    constexpr int i = decltype(ic)::value;
+    constexpr bool kFull = decltype(fullc)::value;
+    const int blk = kMB / 2 * wm + i;
+    const float amax = fmaxf(part[hl][blk][0], part[hl][blk][1]);
+    const float inv = amax > 0.0f ? kQmax / amax : 0.0f;
+    int8_t* tw = reinterpret_cast<int8_t*>(etile(hl * T::kBlocks + blk)) + 64 * half + m;
 #pragma unroll
     for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-      for (int nb = 0; nb < 4; ++nb)
+      for (int nb = 0; nb < kNB; ++nb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = 32 * mi + 8 * (r >> 2) + 4 * hh + (r & 3);
           const float y = (float)(_Float16)acc[2 * i + mi][nb][r];
           const int q = min(119, max(-119, rne_mul(y, inv)));
-          tw[row * kTileStride + 32 * nb + m] = (int8_t)((kFull || row < nv) ? q : 0);
+          tw[row * kTileStride + 32 * nb] = (int8_t)((kFull || row < nv0 - 64 * i) ? q : 0);
         }
-    if (lane == 0) sblk[4 * wn + 2 * wm + i] = sc_[i];
+    // the next block's accumulator reads stay below this point
+    __builtin_amdgcn_sched_barrier(0);
   };
-  // (i a compile-time constant: acc is indexed with it)
   auto run = [&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    if (t0 + 128 * wm + 64 * i + 64 <= a.N)  // wave-uniform
-      block(ic, std::true_type{});
+    if (nv0 >= 64 * decltype(ic)::value + 64)  // wave-uniform
+      codes(ic, std::true_type{});
     else
-      block(ic, std::false_type{});
+      codes(ic, std::false_type{});
   };
   run(std::integral_constant<int, 0>{});
-  // the next block's AGPR reads stay below this point
-  __builtin_amdgcn_sched_barrier(0);
-  run(std::integral_constant<int, 1>{});
+  if constexpr (kMB == 4) run(std::integral_constant<int, 1>{});
   __syncthreads();
+  auto block_scale = [&](int h, int blk) {
+    const float amax = fmaxf(part[h][blk][0], part[h][blk][1]);
+    return amax > 0.0f ? amax / kQmax : 0.0f;
+  };
 
-  // ---- Q8 / K8 / V8 and the block scales: each wave its own two tiles --------
-  if (hv) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int8_t* tw = reinterpret_cast<const int8_t*>(etile(4 * wn + 2 * wm + i));
-      const int jb = (t0 + 128 * wm + 64 * i) / 64;  // FlashQ block index in the sequence
-      if (jb >= a.nb) continue;                      // wave-uniform
-      if (head < a.Hq + a.Hkv) {
+  // ---- Q8 / K8 / V8 and the block scales: kPer waves to a block ---------------
+  {
+    constexpr int kPer = T::kWaves / T::kTiles;
+    const int t = wv / kPer, sub = wv % kPer;
+    const int h = t / T::kBlocks, blk = t % T::kBlocks, hd = head0 + h;
+    const int jb = t0 / 64 + blk;  // FlashQ block index in the sequence
+    const int8_t* tw = reinterpret_cast<const int8_t*>(etile(t));
+    if (hd < nheads && jb < a.nb) {  // wave-uniform
+      const float s = block_scale(h, blk);
+      if (hd < a.Hq + a.Hkv) {
         // token-major int8 rows (Q8 or K8) and the block scale
-        const bool isq = head < a.Hq;
-        const int hq = isq ? head : head - a.Hq;
-        const long unit = (long)b * (isq ? a.Hq : a.Hkv) + hq;
+        const bool isq = hd < a.Hq;
+        const long unit = (long)b * (isq ? a.Hq : a.Hkv) + (isq ? hd : hd - a.Hq);
         int8_t* dst = (isq ? a.q8 : a.k8) + (unit * a.nb + jb) * 8192;
 #pragma unroll
-        for (int it = 0; it < 16; ++it) {
-          const int row = 4 * it + (lane >> 4), c8 = lane & 15;
+        for (int it = 0; it < 16 / kPer; ++it) {
+          const int row = 4 * (it * kPer + sub) + (lane >> 4), c8 = lane & 15;
           *reinterpret_cast<uint2*>(dst + row * 128 + 8 * c8) =
               *reinterpret_cast<const uint2*>(tw + row * kTileStride + 8 * c8);
         }
-        if (lane == 0) (isq ? a.sq : a.sk)[unit * a.nb + jb] = sc_[i];
+        if (lane == 0 && sub == 0) (isq ? a.sq : a.sk)[unit * a.nb + jb] = s;
       } else {
-        // channel-major V8 block: lane = channel pair
-        const long unit = (long)b * a.Hkv + (head - a.Hq - a.Hkv);
+        // channel-major V8 block: a lane writes whole channels
+        const long unit = (long)b * a.Hkv + (hd - a.Hq - a.Hkv);
         int8_t* dst = a.v8 + (unit * a.nb + jb) * 8192;
 #pragma unroll
-        for (int cc = 0; cc < 2; ++cc) {
-          const int c = 2 * lane + cc;
+        for (int cc = 0; cc < 2 / kPer; ++cc) {
+          const int c = kPer == 1 ? 2 * lane + cc : 64 * sub + lane;
           unsigned wd[16];
 #pragma unroll
           for (int k = 0; k < 16; ++k) {
-            const int t = 4 * k;
-            wd[k] = pack4(tw[t * kTileStride + c], tw[(t + 1) * kTileStride + c],
-                          tw[(t + 2) * kTileStride + c], tw[(t + 3) * kTileStride + c]);
+            const int8_t* p = tw + 4 * k * kTileStride + c;
+            wd[k] = pack4(p[0], p[kTileStride], p[2 * kTileStride], p[3 * kTileStride]);
           }
           uint4* o = reinterpret_cast<uint4*>(dst + c * 64);
 #pragma unroll
           for (int k = 0; k < 4; ++k)
             o[k] = make_uint4(wd[4 * k], wd[4 * k + 1], wd[4 * k + 2], wd[4 * k + 3]);
         }
-        if (lane == 0) a.sv[unit * a.nb + jb] = sc_[i];
+        if (lane == 0 && sub == 0) a.sv[unit * a.nb + jb] = s;
       }
     }
   }
 
   // ---- step 2 and the cache write (K and V heads, full blocks) ---------------
   if (a.pages == nullptr) return;  // work-group uniform
-  uint8_t* ctile = etile(8);
-  for (int hl = 0; hl < 2; ++hl) {
-    const int hd = 2 * pair + hl;
+  const int team = tid >> 8, tm = tid & 255;  // 256 threads take a block
+  for (int h = 0; h < T::kHeads; ++h) {
+    const int hd = head0 + h;
     if (hd < a.Hq || hd >= nheads) continue;  // work-group uniform
     const bool isk = hd < a.Hq + a.Hkv;
     const int hkv = isk ? hd - a.Hq : hd - a.Hq - a.Hkv;
     const int bits = ((a.int2_mask >> hkv) & 1ull) ? 2 : 4;
     const int head_off = 512 * (4 * hkv - 2 * __popcll(a.int2_mask & ((1ull << hkv) - 1ull)));
-    for (int w = 0; w < 4; ++w) {
-      const int g = (t0 + 64 * w) / 64;
-      if (t0 + 64 * w + 64 > a.N || g >= a.max_groups) break;  // uniform
-      long page[4];
-      bool ok = true;
-      const int* bt = a.block_table + (long)b * 4 * a.max_groups + 4 * g;
+    for (int w = team; w < T::kBlocks; w += T::kTeams) {
+      const int g = t0 / 64 + w;
+      bool ok = t0 + 64 * w + 64 <= a.N && g < a.max_groups;  // uniform over the team
+      long page[4] = {0, 0, 0, 0};
+      long slot = 0;
+      if (ok) {
+        const int* bt = a.block_table + (long)b * 4 * a.max_groups + 4 * g;
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        page[p] = bt[p];
-        ok = ok && page[p] >= 0 && page[p] < a.num_pages;
+        for (int p = 0; p < 4; ++p) {
+          page[p] = bt[p];
+          ok = ok && page[p] >= 0 && page[p] < a.num_pages;
+        }
+        slot = a.group_table[(long)b * a.max_groups + g];
+        ok = ok && slot >= 0 && slot < a.num_slots;
       }
-      const long slot = a.group_table[(long)b * a.max_groups + g];
-      if (!ok || slot < 0 || slot >= a.num_slots) continue;  // uniform
-      int8_t* meta = a.gmeta + (slot * a.Hkv + hkv) * 512;
-      const int8_t* tb = reinterpret_cast<const int8_t*>(etile(4 * hl + w));
+      int8_t* meta = a.gmeta + ((ok ? slot : 0) * a.Hkv + hkv) * 512;
+      float* gs = a.gscale + ((ok ? slot : 0) * a.Hkv + hkv) * 2;
+      const int8_t* tb = reinterpret_cast<const int8_t*>(etile(h * T::kBlocks + w));
+      const float s = block_scale(h, w);
       if (isk)
-        compress_k(tb, ctile, bits, meta, a.gscale + (slot * a.Hkv + hkv) * 2 + 0, sblk[4 * hl + w],
-                   page, a.pages, a.page_bytes, head_off);
+        compress_k(tb, etile(T::kTiles + team), bits, meta, gs, s, page, a.pages,
+                   a.page_bytes, head_off, tm, ok);
       else
-        compress_v(tb, bits, meta, a.gscale + (slot * a.Hkv + hkv) * 2 + 1, sblk[4 * hl + w], page,
-                   a.pages, a.page_bytes, head_off);
+        compress_v(tb, bits, meta, gs + 1, s, page, a.pages, a.page_bytes, head_off, tm, ok);
       __syncthreads();
     }
   }
 }
 
-hipError_t launch_qkv_project(const QkvArgs& a, hipStream_t stream) {
-  const int total = a.B * a.ntile * ceil_div(a.Hq + 2 * a.Hkv, 2);
+template <typename T>
+static void launch_tiles(const QkvArgs& a, hipStream_t stream) {
+  const dim3 grid(a.B * ceil_div(a.N, T::kTok) * ceil_div(a.Hq + 2 * a.Hkv, T::kHeads));
   if (a.y)
-    hipLaunchKernelGGL(k_qkv_project<true>, dim3(total), dim3(kProjThreads), 0, stream, a);
+    hipLaunchKernelGGL((k_qkv_project<T, true>), grid, dim3(T::kThreads), 0, stream, a);
   else
-    hipLaunchKernelGGL(k_qkv_project<false>, dim3(total), dim3(kProjThreads), 0, stream, a);
+    hipLaunchKernelGGL((k_qkv_project<T, false>), grid, dim3(T::kThreads), 0, stream, a);
+}
+
+// The larger tile is the faster one per token when it fills the chip: a round of
+// 256 of them (one per CU) takes as long as 1.46 rounds of 512 small ones (two
+// per CU), which cover half as much: 105 against 72 us at D = 4096.  So the small
+// tile is taken where it needs clearly fewer rounds, above all where one round of
+// large tiles would leave CUs idle.  Measured (large / small, us; 32 + 2 x 8 heads,
+// D = 4096): 128 tokens 84 / 48, 777 tokens 91 / 58, 2048 tokens 111 / 119, 4096
+// tokens 219 / 215; Phi-3-medium 4 x 4096 tokens 1167 / 1351.
+static bool small_tiles(const QkvArgs& a) {
+  const long nheads = a.Hq + 2 * a.Hkv;
+  auto rounds = [&](int tok, int heads, long slots) {
+    const long tiles = (long)a.B * ceil_div(a.N, tok) * ((nheads + heads - 1) / heads);
+    return (tiles + slots - 1) / slots;
+  };
+  return 72 * rounds(QkvSmall::kTok, QkvSmall::kHeads, 512) <
+         105 * rounds(QkvLarge::kTok, QkvLarge::kHeads, 256);
+}
+
+hipError_t launch_qkv_project(const QkvArgs& a, hipStream_t stream) {
+  if (small_tiles(a))
+    launch_tiles<QkvSmall>(a, stream);
+  else
+    launch_tiles<QkvLarge>(a, stream);
   return hipGetLastError();
 }
 

@@ -1,7 +1,9 @@
 // FlashQ step 2 on an int8 block staged token-major in LDS, and the paged
 // cache writes of its codes (Sec. 3.1 step 2, Algorithm 1): the routines the
 // K/V quantization kernel and the fused QKV projection share.  Each routine is
-// executed by all 256 threads of a work-group.
+// executed by 256 threads, tid 0 .. 255, which all threads of the work-group do
+// together (there is a barrier in compress_k); where active is false (uniform
+// over the 256) nothing is written to memory.
 #pragma once
 
 #include "turbo_common.h"
@@ -14,8 +16,8 @@ constexpr int kTileStride = 136;  // LDS row stride (bytes) of the int8 tile
 // channel c, tokens 32hh..32hh+31 of the LDS tile.  Returns the codes of its
 // 32 tokens in code[] and writes s/z to meta (hh == 0 threads).
 static __device__ void step2_channel(const int8_t* tile, int bits, int8_t* meta_s, int8_t* meta_z,
-                              int* code) {
-  const int tid = threadIdx.x, c = tid >> 1, hh = tid & 1;
+                              int* code, int tid, bool active) {
+  const int c = tid >> 1, hh = tid & 1;
   int q[32];
   int mn = 127, mx = -128;
 #pragma unroll
@@ -33,7 +35,7 @@ static __device__ void step2_channel(const int8_t* tile, int bits, int8_t* meta_
   const int M = (1 << 20) / (2 * s) + 1;
 #pragma unroll
   for (int i = 0; i < 32; ++i) code[i] = ((2 * (q[i] - mn) + s) * M) >> 20;
-  if (hh == 0) {
+  if (active && hh == 0) {
     meta_s[c] = (int8_t)s;
     meta_z[c] = (int8_t)mn;
   }
@@ -44,15 +46,15 @@ static __device__ void step2_channel(const int8_t* tile, int bits, int8_t* meta_
 // the four pages of the group (head region at head_off).
 static __device__ void compress_k(const int8_t* tile, uint8_t* ctile, int bits, int8_t* meta,
                            float* gscale_k, float s, const long (&page)[4], uint8_t* pages,
-                           int page_bytes, int head_off) {
-  const int tid = threadIdx.x;
+                           int page_bytes, int head_off, int tid, bool active = true) {
   int code[32];
-  step2_channel(tile, bits, meta, meta + 128, code);
-  if (tid == 0) *gscale_k = s;
+  step2_channel(tile, bits, meta, meta + 128, code, tid, active);
+  if (active && tid == 0) *gscale_k = s;
   const int c = tid >> 1, hh = tid & 1;
 #pragma unroll
   for (int i = 0; i < 32; ++i) ctile[(32 * hh + i) * kTileStride + c] = (uint8_t)code[i];
   __syncthreads();
+  if (!active) return;
   // token-major packing: thread (t = tid>>2, chunk = tid&3) packs 32 channels
   const int t = tid >> 2, ch = tid & 3;
   const uint8_t* src = ctile + t * kTileStride + 32 * ch;
@@ -83,10 +85,11 @@ static __device__ void compress_k(const int8_t* tile, uint8_t* ctile, int bits, 
 // Step 2 of the V group staged token-major in `tile`, its metadata and float
 // scale, and the channel-major packing of the codes into the group's pages.
 static __device__ void compress_v(const int8_t* tile, int bits, int8_t* meta, float* gscale_v, float s,
-                           const long (&page)[4], uint8_t* pages, int page_bytes, int head_off) {
-  const int tid = threadIdx.x;
+                           const long (&page)[4], uint8_t* pages, int page_bytes, int head_off,
+                           int tid, bool active = true) {
   int code[32];
-  step2_channel(tile, bits, meta + 256, meta + 384, code);
+  step2_channel(tile, bits, meta + 256, meta + 384, code, tid, active);
+  if (!active) return;
   if (tid == 0) *gscale_v = s;
   // channel-major packing: tokens 32hh..32hh+31 are pages 2hh, 2hh+1
   const int c = tid >> 1, hh = tid & 1;

@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kQkvThreads) void k_quantize_kv(QuantArgs a) {
   __syncthreads();
   if (!isv) {
     if (do_cache)
-      compress_k(tile, ctile, bits, meta, gscale, s, page, a.pages, a.page_bytes, head_off);
+      compress_k(tile, ctile, bits, meta, gscale, s, page, a.pages, a.page_bytes, head_off, tid);
     return;
   }
   {
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kQkvThreads) void k_quantize_kv(QuantArgs a) {
     dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
   }
   if (do_cache)
-    compress_v(tile, bits, meta, gscale + 1, s, page, a.pages, a.page_bytes, head_off);
+    compress_v(tile, bits, meta, gscale + 1, s, page, a.pages, a.page_bytes, head_off, tid);
 }
 
 // Step 1 with BC-token blocks (BC = 32 or 128): one workgroup per (b, h,

@@ -284,7 +284,6 @@ static int qkv_project_impl(const void* x, const void* w, int B, int N, int D, i
   a.Hq = Hq;
   a.Hkv = Hkv;
   a.nb = turbo::ceil_div(N, TURBO_BLOCK);
-  a.ntile = (int)ntile;
   a.q8 = q8;
   a.sq = s_q;
   a.k8 = k8;

@@ -96,6 +96,11 @@ EXACT_CASES = [
     (1, 300, 5120, 2, 1, [4]),        # the Phi-3-medium hidden width
     (1, 17, 64, 1, 1, [4]),           # no full group
     (3, 64 * 5, 192, 3, 3, [2, 4, 4]),
+    # enough heads for the 256 x 256 tiles (the cases above take 128 x 128): one,
+    # two and three stages of 64 columns; partial token tiles; an odd head count
+    (1, 300, 64, 128, 64, [4, 2] * 32),
+    (1, 300, 192, 128, 64, [2, 4] * 32),
+    (1, 700, 128, 63, 63, [4] * 62 + [2]),
 ]
 
 
