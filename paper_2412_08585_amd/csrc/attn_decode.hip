@@ -1359,24 +1359,30 @@ static void launch_decode(const DecodeArgs& a, int total, hipStream_t stream) {
 // of its longest one; W waves cut the chain W-fold, at about 2.3 (W = 4) and
 // 3.3 us (W = 8) per step of W groups, since they share the CU's LDS.  A launch
 // that fills the chip anyway is bound by the sum of its work, where W > 1 pays
-// for W prologues and the exchanges.  Measured, us per decoding step (append,
-// decode, merge; int4, 4000 cached tokens in two chunks), W = 1 / 2 / 4 / 8 at
-// GP = 4: 64 chunks 54 / 43 / 31 / 26, 256: 56 / 45 / 34 / 33, 512: 60 / 50 /
-// 40 / 55, 768: 66 / 55 / 49 / 77, 1024: 71 / 62 / 72 / 99, 1536: 85 / 81 / 90 /
-// 143, 2560: 134 / 138 / 145 / 230.  GP = 8 (one wave spills there; it measured
-// 69 at 64 chunks, 78 at 512, 94 at 1024): 64 chunks - / 46 / 33 / 27, 512:
-// - / 56 / 44 / 59, 1024: - / 68 / 78 / 109, and 497 / 389 / 430 / 664 for 8192
-// chunks of 8000 tokens.  Chunks of 48 groups and more spread the prologues over
-// more steps and make the longest chain longer: 1024 chunks of sequences of 256
-// to 16383 tokens (GP = 8) 144 / 92 / 77 / 92, 2048 chunks of 16000 tokens
-// (GP = 16) 365 / 337 / 294 / 352.
+// for W prologues and the exchanges.  So W is the most for which every chunk is
+// resident at once: three waves per SIMD (3072) up to eight rows, two with
+// sixteen, one work-group of eight waves per CU.  Measured, us per decoding step
+// (int4 or mixed, equal sequences), W = 1 / 2 / 4 / 8.  4000 cached tokens in two
+// chunks, GP = 4: 64 chunks 54 / 43 / 31 / 26, 256: 56 / 45 / 34 / 33, 512: 60 /
+// 50 / 40 / 55, 768: 66 / 55 / 49 / 77, 1024: 71 / 62 / 72 / 99, 1536: 85 / 81 /
+// 90 / 143, 2560: 134 / 138 / 145 / 230.  16384 tokens in four, GP = 1: 768: 96 /
+// 79 / 74 / 101, 1024: 98 / 93 / 112 / 132, 1280: 116 / 115 / 123 / 163, 1792:
+// 155 / 189 / 173 / 219; GP = 8: 1024: - / 109 / 127 / 156.  More than four rows
+// in one wave spill (GP = 8: 78 at 512 chunks of 4000 tokens against 56 / 44 / 59
+// for W = 2 / 4 / 8, 497 at 8192 chunks of 8000 against 389), so they take two
+// waves at least.  With them, chunks of 48 groups and more take four waves also
+// where only three quarters are resident at once (all, with sixteen rows: half):
+// 16 % behind two waves if the sequences are equally long, 16 % ahead if they are
+// not (32 sequences of 256 to 16383 tokens, GP = 8: - / 92 / 77 / 92; 2048 chunks
+// of 16000 tokens, GP = 16: - / 337 / 294 / 352).
 static int decode_waves(const DecodeArgs& a) {
   const long units = (long)a.B * a.Hkv * a.nsplit;
+  const long waves = a.G > 8 ? 2048 : 3072;
   const int len = ceil_div(a.max_groups, a.nsplit);  // groups of the longest chunk, or one more
   if (units <= 256 && len >= 8) return 8;
-  if (units <= (len >= 48 ? 2048 : 768) && len >= 4) return 4;
-  if (a.G > 4 || (units <= 1792 && len >= 2)) return 2;
-  return 1;
+  if (4 * units <= waves && len >= 4) return 4;
+  if (a.G > 4) return len >= 48 && units <= (a.G > 8 ? 2048 : 1024) ? 4 : 2;
+  return 2 * units <= waves && len >= 2 ? 2 : 1;
 }
 
 hipError_t launch_attn_decode(const DecodeArgs& a, hipStream_t stream) {
