@@ -1,11 +1,10 @@
 // TurboAttention prefill on gfx950 (Algorithm 1): int8 QK^T and PV on the
 // i8 MFMA, SAS online softmax in fp32 on the VALU.  Two kernels:
-//   * k_attn_prefill16 (further below): B_r = B_c = 64, the paper's setting,
-//     with four waves of 16 query rows -- the default, the pre-quantized-Q
-//     path and the test hook;
-//   * k_attn_prefill (this one): waves of 32 query rows, templated over
-//     B_r in {32, 64, 128} and B_c in {32, 64, 128} for the other block sizes
-//     of Table 3.
+//   * k_attn_prefill16 (further below): waves of 16 query rows, for B_r = 64
+//     (the paper's setting with B_c = 64, the pre-quantized-Q path) and 128
+//     with B_c = 64 and 128;
+//   * k_attn_prefill (this one): waves of 32 query rows, for the other block
+//     sizes of Table 3, B_r = 32 or B_c = 32.
 //
 // k_attn_prefill: a workgroup of B_r / 32 waves owns one (sequence b, query
 // head h, query block i of B_r rows); wave qh holds queries B_r i + 32qh ..
@@ -401,7 +400,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void k_attn_prefill(PrefillArgs a) 
 }
 
 // ---------------------------------------------------------------------------
-// B_r = B_c = 64 (the paper's setting): four waves of 16 query rows.
+// B_r and B_c of at least 64: waves of 16 query rows (four with the paper's
+// B_r = B_c = 64).
 //
 // A 16-row wave holds half the accumulators of a 32-row one, which brings the
 // kernel under 128 VGPRs: a SIMD then keeps four waves resident instead of
@@ -450,21 +450,31 @@ __device__ __forceinline__ uint4 tile_load(__amdgpu_buffer_rsrc_t r, unsigned vo
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-template <int kW>
+// kH 64-key halves per tile, each laid out by itself
+template <int kW, int kH>
 struct Prefill16Lds {
-  __attribute__((aligned(16))) int8_t k[2][64 * 128];   // [key][128 channels], swizzled
-  __attribute__((aligned(16))) int8_t v[2][128 * 64];   // [channel][64 keys], swizzled
+  __attribute__((aligned(16))) int8_t k[2][kH * 64 * 128];  // [key][128 channels], swizzled
+  __attribute__((aligned(16))) int8_t v[2][kH * 128 * 64];  // [channel][64 keys], swizzled
   float lut[8];
   float xmax[2][kW];
   float xq[kW];
 };
 
-// kW waves of 16 rows: B_r = 16 kW (4: the paper's 64; 8: Table 3's 128).
-template <bool kTrace, bool kQ8, int kW>
-__global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
+// kW waves of 16 rows: B_r = 16 kW (4: the paper's 64; 8: Table 3's 128).  kBc =
+// 64 or 128 keys per tile: a 128-key tile is two 64-key halves of the same
+// layouts, with one maximum, one P scale and one accumulator update.  Its 32
+// scores per lane leave two waves per SIMD; held to four it spills (187 us where
+// this runs 153).  Still ahead of 32-row waves with K and V from global memory,
+// us at 40 heads x 3000 tokens / 2 x 16 heads x 700: (128, 128) 153 / 25 against
+// 181 / 41, (64, 128) 147 / 23 against 166 / 37.  With B_r = 32 it is behind on
+// the large input (two waves share a tile: 151 against 148 at B_c = 64, 225
+// against 153 at 128), so that stays with 32-row waves.
+template <bool kTrace, bool kQ8, int kW, int kBc = 64>
+__global__ __launch_bounds__(64 * kW, kBc == 128 ? 2 : 4) void k_attn_prefill16(PrefillArgs a) {
   static_assert(kW == 4 || kW == 8, "B_r = 64 or 128");
-  constexpr int kBr = 16 * kW;
-  __shared__ Prefill16Lds<kW> L;
+  static_assert(kBc == 64 || kBc == 128, "B_c");
+  constexpr int kBr = 16 * kW, kH = kBc / 64;
+  __shared__ Prefill16Lds<kW, kH> L;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
@@ -486,45 +496,40 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
   const cfloat* skp = (const cfloat*)(a.sk + kvu * a.nbc);
   const cfloat* svp = (const cfloat*)(a.sv + kvu * a.nbc);
   // last key tile: the one holding the block's last row when causal
-  const int jend = a.causal ? min(a.nbc - 1, (kBr * i + kBr - 1) / 64) : a.nbc - 1;
+  const int jend = a.causal ? min(a.nbc - 1, (kBr * i + kBr - 1) / kBc) : a.nbc - 1;
 
-  // ---- tile copies: the 512 16-byte chunks of a K (V) tile, one (kW = 8)
-  // or two (kW = 4: tid and tid + 256) per thread --------------------------
-  // wave-uniform tile bases; the lane adds its chunk index
-  constexpr bool kTwo = kW == 4;
-  const uint4* kg = reinterpret_cast<const uint4*>(a.k8 + kvu * a.nb * 8192);
-  const uint4* vg = reinterpret_cast<const uint4*>(a.v8 + kvu * a.nb * 8192);
-  const int c0 = tid, c1 = tid + 256;
-  // buffer resources over this unit's K8 and V8 blocks (loads past them,
-  // which never occur, would read 0)
+  // ---- tile copies: the 512 kH 16-byte chunks of a K (V) tile, kC per thread
+  // (tid, tid + 64 kW, ..) ---------------------------------------------------
+  constexpr int kC = 512 * kH / (64 * kW), kStep = 64 * kW;
+  // buffer resources over this unit's K8 and V8 blocks: a 128-key tile can
+  // reach one 64-key block past them and then reads zeros, for keys that are
+  // all >= N and masked
   const __amdgpu_buffer_rsrc_t krs = unit_rsrc(a.k8 + kvu * a.nb * 8192, a.nb * 8192);
   const __amdgpu_buffer_rsrc_t vrs = unit_rsrc(a.v8 + kvu * a.nb * 8192, a.nb * 8192);
   const unsigned lane16 = 16u * (unsigned)tid;
-  const int kdst0 = (c0 >> 3) * 128 + 16 * ((c0 & 7) ^ kswz(c0 >> 3));
-  const int kdst1 = (c1 >> 3) * 128 + 16 * ((c1 & 7) ^ kswz(c1 >> 3));
-  const int vdst0 = (c0 >> 2) * 64 + 16 * ((c0 & 3) ^ vswz(c0 >> 2));
-  const int vdst1 = (c1 >> 2) * 64 + 16 * ((c1 & 3) ^ vswz(c1 >> 2));
+  int kdst[kC], vdst[kC];
+#pragma unroll
+  for (int u = 0; u < kC; ++u) {
+    const int c = tid + kStep * u, q = c & 511;  // chunk within its half
+    kdst[u] = (c >> 9) * 8192 + (q >> 3) * 128 + 16 * ((q & 7) ^ kswz(q >> 3));
+    vdst[u] = (c >> 9) * 8192 + (q >> 2) * 64 + 16 * ((q & 3) ^ vswz(q >> 2));
+  }
   // K_{j+1} and V_{j+1} in flight (registers)
-  uint4 kp0 = kg[tid], vp0 = vg[tid], kp1 = {}, vp1 = {};
-  if constexpr (kTwo) {
-    kp1 = kg[tid + 256];
-    vp1 = vg[tid + 256];
-  }
-  *reinterpret_cast<uint4*>(&L.k[0][kdst0]) = kp0;
-  *reinterpret_cast<uint4*>(&L.v[0][vdst0]) = vp0;
-  if constexpr (kTwo) {
-    *reinterpret_cast<uint4*>(&L.k[0][kdst1]) = kp1;
-    *reinterpret_cast<uint4*>(&L.v[0][vdst1]) = vp1;
-  }
-  {
-    const long o1 = (long)min(1, jend) * 512;
-    kp0 = kg[o1 + tid];
-    vp0 = vg[o1 + tid];
-    if constexpr (kTwo) {
-      kp1 = kg[o1 + tid + 256];
-      vp1 = vg[o1 + tid + 256];
-    }
-  }
+  uint4 kp[kC], vp[kC];
+  auto load_tile = [&](__amdgpu_buffer_rsrc_t r, uint4 (&x)[kC], int j) {
+#pragma unroll
+    for (int u = 0; u < kC; ++u) x[u] = tile_load(r, lane16 + 16u * kStep * u, j * (8192 * kH));
+  };
+  auto store_tile = [&](int8_t* dst, const int (&d)[kC], const uint4 (&x)[kC]) {
+#pragma unroll
+    for (int u = 0; u < kC; ++u) *reinterpret_cast<uint4*>(dst + d[u]) = x[u];
+  };
+  load_tile(krs, kp, 0);
+  load_tile(vrs, vp, 0);
+  store_tile(L.k[0], kdst, kp);
+  store_tile(L.v[0], vdst, vp);
+  load_tile(krs, kp, min(1, jend));
+  load_tile(vrs, vp, min(1, jend));
 
   // ---- Q_i -> int8 (eq. step1bpq; scale over the 64-row block) ----------
   // lane (n, g), k-step ks: channels 64ks + 16g .. +15 of query qrow
@@ -624,58 +629,57 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
     // raised issue priority: a wave that reaches them goes ahead of the
     // softmax arithmetic of the other waves of its SIMD, so that its MFMAs
     // overlap their VALU work.
-    v4i S[4];
+    v4i S[4 * kH];  // block mb of half hb: S[4 hb + mb]
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      const v4i k0 = *reinterpret_cast<const v4i*>(&L.k[buf][kbase0 + 512 * mb]);
-      const v4i k1 = *reinterpret_cast<const v4i*>(&L.k[buf][kbase1 + 512 * mb]);
+    for (int mb = 0; mb < 4 * kH; ++mb) {
+      const int off = 8192 * (mb >> 2) + 512 * (mb & 3);
+      const v4i k0 = *reinterpret_cast<const v4i*>(&L.k[buf][kbase0 + off]);
+      const v4i k1 = *reinterpret_cast<const v4i*>(&L.k[buf][kbase1 + off]);
       v4i acc = {kAccSeed, kAccSeed, kAccSeed, kAccSeed};
       acc = mfma16x16x64(k0, qop[0], acc);
       acc = mfma16x16x64(k1, qop[1], acc);
       S[mb] = acc;
     }
-    *reinterpret_cast<uint4*>(&L.k[buf ^ 1][kdst0]) = kp0;
-    if constexpr (kTwo) *reinterpret_cast<uint4*>(&L.k[buf ^ 1][kdst1]) = kp1;
+    store_tile(L.k[buf ^ 1], kdst, kp);
     // tile j + 2: buffer loads with the tile offset in a scalar register and
     // the lane's fixed offset in a vector register (no per-lane address
     // arithmetic per tile)
-    const int o2 = min(j + 2, jend) * 8192;
-    kp0 = tile_load(krs, lane16, o2);
-    if constexpr (kTwo) kp1 = tile_load(krs, lane16 + 4096u, o2);
+    const int j2 = min(j + 2, jend);
+    load_tile(krs, kp, j2);
     __builtin_amdgcn_s_setprio(0);
     const bool trace_tile = traced && j == a.tr_j;
     if constexpr (kTrace) {
       if (trace_tile) {
-        int* ts = reinterpret_cast<int*>(a.trace + TURBO_TRACE_S) + (16 * w + n) * 64 + 16 * g;
+        int* ts = reinterpret_cast<int*>(a.trace + TURBO_TRACE_S) + (16 * w + n) * kBc + 16 * g;
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int mb = 0; mb < 4 * kH; ++mb)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) ts[4 * mb + r] = S[mb][r] - kAccSeed;
+          for (int r = 0; r < 4; ++r) ts[64 * (mb >> 2) + 4 * (mb & 3) + r] = S[mb][r] - kAccSeed;
       }
     }
     // ---- scores, online max, SAS (Algorithm 1, statistics step) --------
     // (seed - S read as float) * (-c 2^26) = float(S) * c, rounded once
     const float nc26 = -((sq * skj) * sm26);
-    float P[4][4];
+    float P[4 * kH][4];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < 4 * kH; ++mb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) P[mb][r] = acc_unseed_neg(S[mb][r]) * nc26;
     // masking on the diagonal tile and where keys or rows reach past N
-    if ((a.causal && 64 * j + 63 > row0) || (64 * j + 64 > N) || (row0 + 16 > N)) {
+    if ((a.causal && kBc * j + kBc - 1 > row0) || (kBc * j + kBc > N) || (row0 + 16 > N)) {
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < 4 * kH; ++mb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int key = 64 * j + 16 * g + 4 * mb + r;
+          const int key = kBc * j + 64 * (mb >> 2) + 16 * g + 4 * (mb & 3) + r;
           const bool vis = key < N && qrow < N && (!a.causal || key <= qrow);
           P[mb][r] = vis ? P[mb][r] : -INFINITY;
         }
     }
     float smax = -INFINITY;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < 4 * kH; ++mb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) smax = fmaxf(smax, P[mb][r]);
     // scores and maxima are never NaN: maxima without canonicalization
@@ -689,7 +693,7 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
     const bool top = __builtin_amdgcn_ballot_w64(smax >= mold) != 0;
     float rs;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < 4 * kH; ++mb)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const float p = sas_y(mnew - P[mb][r], L.lut);
@@ -713,7 +717,7 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
       // P~ >= 0: the maximum on the bits (integer order = float order)
       int pm = __float_as_int(P[0][0]);
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < 4 * kH; ++mb)
 #pragma unroll
         for (int r = (mb == 0); r < 4; ++r) pm = max(pm, __float_as_int(P[mb][r]));
       pmax = wave_max_pos(__int_as_float(pm));
@@ -753,14 +757,17 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
     // with the rounded reciprocal is within one ulp of the quotient; the
     // factor 2^26 undoes the accumulator seed
     const float ng26 = -(((pmax * (0x1p26f / kQmax)) * svj) * rbeta);
-    v4i pop;
+    v4i pop[kH];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-      pop[mb] = pack_lo4(rne_bits(P[mb][0], inv), rne_bits(P[mb][1], inv),
+    for (int mb = 0; mb < 4 * kH; ++mb)
+      pop[mb >> 2][mb & 3] = pack_lo4(rne_bits(P[mb][0], inv), rne_bits(P[mb][1], inv),
                          rne_bits(P[mb][2], inv), rne_bits(P[mb][3], inv));
     if constexpr (kTrace) {
       if (trace_tile) {
-        *reinterpret_cast<v4i*>(a.trace + TURBO_TRACE_P + (16 * w + n) * 64 + 16 * g) = pop;
+#pragma unroll
+        for (int hb = 0; hb < kH; ++hb)
+          *reinterpret_cast<v4i*>(a.trace + TURBO_TRACE_P + (16 * w + n) * kBc + 64 * hb + 16 * g) =
+              pop[hb];
         if (tid == 0) *reinterpret_cast<float*>(a.trace + TURBO_TRACE_PMAX) = pmax;
       }
     }
@@ -773,9 +780,13 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        const v4i vop = *reinterpret_cast<const v4i*>(&L.v[buf][vbase + 1024 * (4 * hv + c)]);
-        const v4i z = {kAccSeed, kAccSeed, kAccSeed, kAccSeed};
-        acc[c] = mfma16x16x64(vop, pop, z);
+        acc[c] = v4i{kAccSeed, kAccSeed, kAccSeed, kAccSeed};
+#pragma unroll
+        for (int hb = 0; hb < kH; ++hb) {
+          const v4i vop =
+              *reinterpret_cast<const v4i*>(&L.v[buf][8192 * hb + vbase + 1024 * (4 * hv + c)]);
+          acc[c] = mfma16x16x64(vop, pop[hb], acc[c]);
+        }
       }
       __builtin_amdgcn_s_setprio(0);
       if constexpr (kTrace) {
@@ -795,10 +806,8 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
           O[4 * hv + c][r] = __builtin_fmaf(ng26, acc_unseed_neg(acc[c][r]), O[4 * hv + c][r]);
       __builtin_amdgcn_sched_barrier(0);
     }
-    *reinterpret_cast<uint4*>(&L.v[buf ^ 1][vdst0]) = vp0;
-    if constexpr (kTwo) *reinterpret_cast<uint4*>(&L.v[buf ^ 1][vdst1]) = vp1;
-    vp0 = tile_load(vrs, lane16, o2);
-    if constexpr (kTwo) vp1 = tile_load(vrs, lane16 + 4096u, o2);
+    store_tile(L.v[buf ^ 1], vdst, vp);
+    load_tile(vrs, vp, j2);
     skj = skn;
     svj = svn;
   };
@@ -835,33 +844,37 @@ __global__ __launch_bounds__(64 * kW, 4) void k_attn_prefill16(PrefillArgs a) {
   }
 }
 
-template <bool kTrace, int kWaves>
-static void launch_bc(const PrefillArgs& a, int total, hipStream_t stream) {
-  const dim3 grid(total), block(64 * kWaves);
-  if (a.bc == 32)
-    hipLaunchKernelGGL((k_attn_prefill<kTrace, false, kWaves, 32>), grid, block, 0, stream, a);
-  else if (a.bc == 128)
-    hipLaunchKernelGGL((k_attn_prefill<kTrace, false, kWaves, 128>), grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL((k_attn_prefill<kTrace, false, kWaves, 64>), grid, block, 0, stream, a);
-}
-
-// (B_r, B_c) = (64, 64) and (128, 64) run on the 16-row-wave kernel, the
-// other pairs on the 32-row-wave kernel; the test hook runs the same kernel
-// as the plain call (its trace instance).
+// B_r >= 64 with B_c >= 64 runs on the 16-row-wave kernel, the other block sizes
+// on the 32-row-wave kernel; the test hook runs the same kernel as the plain
+// call (its trace instance).
 template <bool kTrace>
 static void launch_prefill(const PrefillArgs& a, hipStream_t stream) {
-  const int total = a.B * a.Hq * a.nbq;
-  if (a.waves == 2 && a.bc == 64)
-    hipLaunchKernelGGL((k_attn_prefill16<kTrace, false, 4>), dim3(total), dim3(256), 0, stream, a);
-  else if (a.waves == 4 && a.bc == 64)
-    hipLaunchKernelGGL((k_attn_prefill16<kTrace, false, 8>), dim3(total), dim3(512), 0, stream, a);
-  else if (a.waves == 1)
-    launch_bc<kTrace, 1>(a, total, stream);
-  else if (a.waves == 4)
-    launch_bc<kTrace, 4>(a, total, stream);
-  else
-    launch_bc<kTrace, 2>(a, total, stream);
+  const dim3 grid(a.B * a.Hq * a.nbq);
+  if (a.waves == 1) {
+    const dim3 block(64);
+    if (a.bc == 32)
+      hipLaunchKernelGGL((k_attn_prefill<kTrace, false, 1, 32>), grid, block, 0, stream, a);
+    else if (a.bc == 64)
+      hipLaunchKernelGGL((k_attn_prefill<kTrace, false, 1, 64>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((k_attn_prefill<kTrace, false, 1, 128>), grid, block, 0, stream, a);
+  } else if (a.waves == 2) {
+    const dim3 block(a.bc == 32 ? 128 : 256);
+    if (a.bc == 32)
+      hipLaunchKernelGGL((k_attn_prefill<kTrace, false, 2, 32>), grid, block, 0, stream, a);
+    else if (a.bc == 64)
+      hipLaunchKernelGGL((k_attn_prefill16<kTrace, false, 4>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((k_attn_prefill16<kTrace, false, 4, 128>), grid, block, 0, stream, a);
+  } else {
+    const dim3 block(a.bc == 32 ? 256 : 512);
+    if (a.bc == 32)
+      hipLaunchKernelGGL((k_attn_prefill<kTrace, false, 4, 32>), grid, block, 0, stream, a);
+    else if (a.bc == 64)
+      hipLaunchKernelGGL((k_attn_prefill16<kTrace, false, 8>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((k_attn_prefill16<kTrace, false, 8, 128>), grid, block, 0, stream, a);
+  }
 }
 
 hipError_t launch_attn_prefill(const PrefillArgs& a, hipStream_t stream) {
