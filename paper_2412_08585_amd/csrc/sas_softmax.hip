@@ -6,10 +6,8 @@
 // The operation reads and writes each element once, so it is bound by HBM.
 // Rows of up to 2048 values are held in the registers of one wave (four
 // rows per work-group); longer rows use one 256-thread work-group, in
-// registers up to 16384 values (17405 in rows that are not 16-byte aligned) and
-// in three streaming passes beyond.
+// registers up to 16384 values and in three streaming passes beyond.
 #include "turbo_common.h"
-#include "stream_loads.h"
 
 namespace turbo {
 
@@ -18,6 +16,7 @@ struct SasSoftmaxArgs {
   float* y;        // [rows][cols]
   long rows;
   int cols;
+  int vec;         // 0: short rows that are not 16-byte aligned, read and written value by value
 };
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -31,73 +30,48 @@ __device__ __forceinline__ float wave_sum(float v) {
   return add_xor32(v);
 }
 
-// How a row lies in memory.  Its chunks of four values are the 16-byte units
-// of the address space it touches, so that every whole chunk is one vector
-// access wherever the row starts: a row of a ragged matrix starts up to 3 values
-// into its first unit.  40040 rows of 1001: 55.5 us, 5.8 TB/s, against 91 us with
-// scalar accesses wherever cols % 4 != 0.
-template <bool kShift>
-struct Row {
-  const float* x;
-  float* y;
-  int C;
-  int sx;   // values before the row in its first 16-byte unit (kShift)
-  bool vy;  // the output row lies likewise: vector stores
+// Four values that start on any 4-byte boundary: global memory takes a 16-byte
+// access there, so the rows of a ragged matrix are read and written in vectors
+// too (40040 rows of 1001: 56 us, 5.7 TB/s, against 91 us value by value; 20000
+// of 2047 62 / 95, 3000 of 16383 74 / 105).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
-  __device__ __forceinline__ Row(const SasSoftmaxArgs& a, long row)
-      : x(a.x + row * a.cols), y(a.y + row * a.cols), C(a.cols), sx(0), vy(true) {
-    if constexpr (kShift) {
-      sx = (int)(reinterpret_cast<uintptr_t>(x) >> 2) & 3;
-      vy = ((int)(reinterpret_cast<uintptr_t>(y) >> 2) & 3) == sx;
-    }
+// A row in chunks of four values: chunk i of thread t covers columns
+// 4 (t + T i) .. +3, wherever the row lies in memory, so that the order of its
+// sum depends on the number of columns alone.  Columns past the row read as
+// -inf.  kNT: the row is read once (held in registers), so the vector loads
+// stream.
+template <int T, bool kNT = false>
+__device__ __forceinline__ float4 load4(const float* xr, int C, int t, int i, bool vec = true) {
+  const int c = 4 * (t + T * i);
+  if (vec && c + 3 < C) {
+    const f32x4_any* p = reinterpret_cast<const f32x4_any*>(xr + c);
+    const f32x4_any u = kNT ? __builtin_nontemporal_load(p) : *p;
+    return make_float4(u.x, u.y, u.z, u.w);
   }
-  // first column of chunk i of thread t (T threads); it may be negative
-  template <int T>
-  __device__ __forceinline__ int col(int t, int i) const {
-    return 4 * (t + T * i) - (kShift ? sx : 0);
-  }
-  __device__ __forceinline__ bool whole(int c) const {
-    return (!kShift || c >= 0) && c + 3 < C;
-  }
-  __device__ __forceinline__ bool has(int c) const { return (!kShift || c >= 0) && c < C; }
-};
-
-// Chunk i of thread t; columns outside the row read as -inf.  kNT: the row is
-// read once (held in registers), so the vector loads stream.
-template <int T, bool kNT, bool kShift>
-__device__ __forceinline__ float4 load4(const Row<kShift>& r, int t, int i) {
-  const int c = r.template col<T>(t, i);
-  if (r.whole(c)) {
-    if (kNT) {
-      const u32x4_t u = load_nt4(r.x + c);
-      return make_float4(__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z),
-                         __uint_as_float(u.w));
-    }
-    return *reinterpret_cast<const float4*>(r.x + c);
-  }
-  float4 v;
-  v.x = r.has(c) ? r.x[c] : -INFINITY;
-  v.y = r.has(c + 1) ? r.x[c + 1] : -INFINITY;
-  v.z = r.has(c + 2) ? r.x[c + 2] : -INFINITY;
-  v.w = r.has(c + 3) ? r.x[c + 3] : -INFINITY;
-  return v;
+  float4 r;
+  r.x = c < C ? xr[c] : -INFINITY;
+  r.y = c + 1 < C ? xr[c + 1] : -INFINITY;
+  r.z = c + 2 < C ? xr[c + 2] : -INFINITY;
+  r.w = c + 3 < C ? xr[c + 3] : -INFINITY;
+  return r;
 }
 
 // Stores of one output row in the same chunks.  The output is written once
 // and not read again by this launch, so the vector stores stream
 // (non-temporal): 3-4 % faster on the 2.7 GB workload.
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-template <int T, bool kShift>
-__device__ __forceinline__ void store4(const Row<kShift>& r, int t, int i, float4 v) {
-  const int c = r.template col<T>(t, i);
-  if (r.vy && r.whole(c)) {
-    __builtin_nontemporal_store(f32x4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4_t*>(r.y + c));
+template <int T>
+__device__ __forceinline__ void store4(float* yr, int C, int t, int i, float4 v, bool vec = true) {
+  const int c = 4 * (t + T * i);
+  if (vec && c + 3 < C) {
+    __builtin_nontemporal_store(f32x4_any{v.x, v.y, v.z, v.w},
+                                reinterpret_cast<f32x4_any*>(yr + c));
     return;
   }
-  if (r.has(c)) r.y[c] = v.x;
-  if (r.has(c + 1)) r.y[c + 1] = v.y;
-  if (r.has(c + 2)) r.y[c + 2] = v.z;
-  if (r.has(c + 3)) r.y[c + 3] = v.w;
+  if (c < C) yr[c] = v.x;
+  if (c + 1 < C) yr[c + 1] = v.y;
+  if (c + 2 < C) yr[c + 2] = v.z;
+  if (c + 3 < C) yr[c + 3] = v.w;
 }
 
 __device__ __forceinline__ float4 sas4(float m, float4 v, const float* lut) {
@@ -110,7 +84,7 @@ __device__ __forceinline__ float4 div4(float4 v, float s) {
 }
 
 // One wave per row, the row in registers: NV chunks of four per lane.
-template <int NV, bool kShift>
+template <int NV>
 __global__ __launch_bounds__(256) void k_sas_softmax_wave(SasSoftmaxArgs a) {
   __shared__ float lut[8];
   if (threadIdx.x < 8) lut[threadIdx.x] = kLut[threadIdx.x];
@@ -118,14 +92,16 @@ __global__ __launch_bounds__(256) void k_sas_softmax_wave(SasSoftmaxArgs a) {
   const int lane = threadIdx.x & 63;
   const long row = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= a.rows) return;  // wave-uniform; no barrier follows
-  const Row<kShift> r(a, row);
+  const float* xr = a.x + row * a.cols;
+  float* yr = a.y + row * a.cols;
+  const bool vec = NV > 1 || a.vec;
   float4 v[NV];
   float m = -INFINITY;
   // The row's loads are issued at raised priority, ahead of the arithmetic
   // of the other waves of the SIMD.
   __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-  for (int i = 0; i < NV; ++i) v[i] = load4<64, true>(r, lane, i);
+  for (int i = 0; i < NV; ++i) v[i] = load4<64, true>(xr, a.cols, lane, i, vec);
   __builtin_amdgcn_s_setprio(0);
 #pragma unroll
   for (int i = 0; i < NV; ++i)
@@ -139,7 +115,7 @@ __global__ __launch_bounds__(256) void k_sas_softmax_wave(SasSoftmaxArgs a) {
   }
   s = wave_sum(s);
 #pragma unroll
-  for (int i = 0; i < NV; ++i) store4<64>(r, lane, i, div4(v[i], s));
+  for (int i = 0; i < NV; ++i) store4<64>(yr, a.cols, lane, i, div4(v[i], s), vec);
 }
 
 __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) {
@@ -155,7 +131,7 @@ __device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) 
 
 // One 256-thread work-group per row.  NV > 0: the row in registers (NV
 // chunks of four per thread); NV == 0: three passes over memory.
-template <int NV, bool kShift>
+template <int NV>
 __global__ __launch_bounds__(256) void k_sas_softmax_block(SasSoftmaxArgs a) {
   __shared__ float lut[8];
   __shared__ float red[4];
@@ -163,21 +139,24 @@ __global__ __launch_bounds__(256) void k_sas_softmax_block(SasSoftmaxArgs a) {
   if (t < 8) lut[t] = kLut[t];
   __syncthreads();
   const long row = blockIdx.x;
-  const Row<kShift> r(a, row);
-  const int nch = (a.cols + (kShift ? r.sx : 0) + 1023) / 1024;  // chunks of four per thread
+  const float* xr = a.x + row * a.cols;
+  float* yr = a.y + row * a.cols;
+  const int C = a.cols;
+  const int nch = (C + 1023) / 1024;  // chunks of four per thread
   if (NV > 0) {
     float4 v[NV > 0 ? NV : 1];
     float m = -INFINITY;
+    // In a launch of more work-groups than are resident (eight per CU) a wave
+    // takes the chunks of a row of up to 8192 values one after the other: the
+    // other rows keep the memory busy, and 163840 rows of 4096 run 874 us instead
+    // of 915, 5000 of 8191 58 instead of 62.  Fewer rows (64 of 8192: 6.4 against
+    // 5.6 us) and longer ones load all chunks at once.
+    const bool serial = NV <= 8 && gridDim.x > 2048;
     __builtin_amdgcn_s_setprio(2);  // the row's loads first (2 % on 4096-column rows)
-    // Up to 8192 aligned values a wave takes its chunks one after the other:
-    // the row's other waves keep the memory busy, and rows of 4096 run 858 us
-    // instead of 889 (163840 rows), rows of 8192 111 instead of 116 (10000).
-    // Longer rows (16384: 131 against 120 us) and shifted ones (2049: 68 / 65)
-    // load all chunks at once.
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      v[i] = load4<256, true>(r, t, i);
-      if (!kShift && NV <= 8) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (i > 0 && serial) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      v[i] = load4<256, true>(xr, C, t, i);
     }
     __builtin_amdgcn_s_setprio(0);
 #pragma unroll
@@ -192,55 +171,54 @@ __global__ __launch_bounds__(256) void k_sas_softmax_block(SasSoftmaxArgs a) {
     }
     s = block_reduce(s, red, false);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) store4<256>(r, t, i, div4(v[i], s));
+    for (int i = 0; i < NV; ++i) store4<256>(yr, C, t, i, div4(v[i], s));
   } else {
     float m = -INFINITY;
     for (int i = 0; i < nch; ++i) {
-      const float4 v = load4<256, false>(r, t, i);
+      const float4 v = load4<256>(xr, C, t, i);
       m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
     }
     m = block_reduce(m, red, true);
     float s = 0.0f;
     for (int i = 0; i < nch; ++i) {
-      const float4 e = sas4(m, load4<256, false>(r, t, i), lut);
+      const float4 e = sas4(m, load4<256>(xr, C, t, i), lut);
       s += (e.x + e.y) + (e.z + e.w);
     }
     s = block_reduce(s, red, false);
     for (int i = 0; i < nch; ++i)
-      store4<256>(r, t, i, div4(sas4(m, load4<256, false>(r, t, i), lut), s));
+      store4<256>(yr, C, t, i, div4(sas4(m, load4<256>(xr, C, t, i), lut), s));
   }
 }
 
-template <bool kShift>
-static void launch_softmax(const SasSoftmaxArgs& a, hipStream_t stream) {
-  const int C = a.cols + (kShift ? 3 : 0);  // values in the chunks of a row, at most
-  const dim3 wgrid((unsigned)((a.rows + 3) / 4)), bgrid((unsigned)a.rows), block(256);
-  if (C <= 256)
-    hipLaunchKernelGGL((k_sas_softmax_wave<1, kShift>), wgrid, block, 0, stream, a);
-  else if (C <= 512)
-    hipLaunchKernelGGL((k_sas_softmax_wave<2, kShift>), wgrid, block, 0, stream, a);
-  else if (C <= 1024)
-    hipLaunchKernelGGL((k_sas_softmax_wave<4, kShift>), wgrid, block, 0, stream, a);
-  else if (C <= 2048)
-    hipLaunchKernelGGL((k_sas_softmax_wave<8, kShift>), wgrid, block, 0, stream, a);
-  else if (C <= 4096)
-    hipLaunchKernelGGL((k_sas_softmax_block<4, kShift>), bgrid, block, 0, stream, a);
-  else if (C <= 8192)
-    hipLaunchKernelGGL((k_sas_softmax_block<8, kShift>), bgrid, block, 0, stream, a);
-  else if (C <= (kShift ? 17408 : 16384))  // a shifted row of 16384 needs one more chunk
-    hipLaunchKernelGGL((k_sas_softmax_block<kShift ? 17 : 16, kShift>), bgrid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL((k_sas_softmax_block<0, kShift>), bgrid, block, 0, stream, a);
-}
-
-hipError_t launch_sas_softmax(const SasSoftmaxArgs& a, hipStream_t stream) {
-  // rows that all start on a 16-byte unit need no per-row shift
-  const bool aligned = a.cols % 4 == 0 && reinterpret_cast<uintptr_t>(a.x) % 16 == 0 &&
+// Rows of up to 136 values that do not all start on a 16-byte boundary fill few
+// lanes and take single accesses: 100000 rows of 97: 28.1 us against 31.6 with
+// vectors, of 129 31.0 / 34.2, of 137 34.4 / 34.2, of 191 42.7 / 36.5.
+hipError_t launch_sas_softmax(SasSoftmaxArgs a, hipStream_t stream) {
+  const int C = a.cols;
+  const bool aligned = C % 4 == 0 && reinterpret_cast<uintptr_t>(a.x) % 16 == 0 &&
                        reinterpret_cast<uintptr_t>(a.y) % 16 == 0;
-  if (aligned)
-    launch_softmax<false>(a, stream);
-  else
-    launch_softmax<true>(a, stream);
+  a.vec = aligned || C > 136;
+  if (C <= 2048) {
+    const dim3 grid((unsigned)((a.rows + 3) / 4));
+    if (C <= 256)
+      hipLaunchKernelGGL(k_sas_softmax_wave<1>, grid, dim3(256), 0, stream, a);
+    else if (C <= 512)
+      hipLaunchKernelGGL(k_sas_softmax_wave<2>, grid, dim3(256), 0, stream, a);
+    else if (C <= 1024)
+      hipLaunchKernelGGL(k_sas_softmax_wave<4>, grid, dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL(k_sas_softmax_wave<8>, grid, dim3(256), 0, stream, a);
+  } else {
+    const dim3 grid((unsigned)a.rows);
+    if (C <= 4096)
+      hipLaunchKernelGGL(k_sas_softmax_block<4>, grid, dim3(256), 0, stream, a);
+    else if (C <= 8192)
+      hipLaunchKernelGGL(k_sas_softmax_block<8>, grid, dim3(256), 0, stream, a);
+    else if (C <= 16384)
+      hipLaunchKernelGGL(k_sas_softmax_block<16>, grid, dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL(k_sas_softmax_block<0>, grid, dim3(256), 0, stream, a);
+  }
   return hipGetLastError();
 }
 

@@ -97,6 +97,24 @@ def test_sas_softmax_rows_that_start_anywhere(orc, ta, dev, cols, xo, yo):
     assert bool((yb[:yo] == -7.0).all()) and bool((yb[yo + rows * cols:] == -7.0).all())
 
 
+# below and past the width that takes vector accesses; one and several chunks a lane;
+# one work-group per row, in registers and in passes over memory
+@pytest.mark.parametrize("cols", [1, 3, 97, 135, 137, 138, 139, 1001, 2047, 3001, 8190, 16383, 16386])
+def test_sas_softmax_bits_do_not_depend_on_where_a_row_lies(ta, dev, cols):
+    """Equal rows give equal bits in every row of a matrix and wherever it starts."""
+    rows = 9
+    _log(f"sas_softmax equal rows cols={cols}")
+    row = _scores(1, cols, cols)
+    want = None
+    for off in range(4):
+        buf = torch.empty(rows * cols + 4, dtype=torch.float32, device=dev)
+        x = buf[off:off + rows * cols].view(rows, cols)
+        x.copy_(row.expand(rows, cols))
+        y = ta.turbo_sas_softmax(x).view(torch.int32)
+        want = y[:1].clone() if want is None else want
+        assert torch.equal(y, want.expand(rows, cols)), off
+
+
 def test_sas_softmax_in_place_and_single_survivor(orc, ta, dev):
     """In place (y aliases x); a row whose other entries all lie more than 6
     below its maximum is exactly one-hot."""
