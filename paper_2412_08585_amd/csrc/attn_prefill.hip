@@ -439,14 +439,26 @@ __device__ __forceinline__ int vswz(int ch) {
   return (((ch >> 1) ^ (ch >> 3)) & 1) | (((ch >> 2) & 1) << 1);
 }
 
-// Raw buffer resource over `bytes` bytes at p (gfx9 descriptor word 3).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t unit_rsrc(const int8_t* p, int bytes) {
+// Bytes of key tile j (kH blocks of 64 keys, 8 KB each) within the K8 (V8) blocks
+// of one unit, nb of them.  The offset passes 2^31 at 2^24 tokens.  A 128-key tile
+// can reach one block past the last: it then spans that one alone.
+struct TileSpan {
+  long offset;
+  int bytes;
+};
+__host__ __device__ constexpr TileSpan tile_span(int nb, int kH, int j) {
+  return {(long)j * (8192 * kH), 8192 * (nb - j * kH < kH ? nb - j * kH : kH)};
+}
+
+// Raw buffer resource over `bytes` bytes at p (gfx9 descriptor word 3); loads past
+// them return zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const int8_t* p, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(p), 0, bytes, 0x00020000);
 }
 
-__device__ __forceinline__ uint4 tile_load(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff) {
+__device__ __forceinline__ uint4 tile_load(__amdgpu_buffer_rsrc_t r, unsigned voff) {
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, soff, 0);
+  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0);
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
@@ -501,11 +513,8 @@ __global__ __launch_bounds__(64 * kW, kBc == 128 ? 2 : 4) void k_attn_prefill16(
   // ---- tile copies: the 512 kH 16-byte chunks of a K (V) tile, kC per thread
   // (tid, tid + 64 kW, ..) ---------------------------------------------------
   constexpr int kC = 512 * kH / (64 * kW), kStep = 64 * kW;
-  // buffer resources over this unit's K8 and V8 blocks: a 128-key tile can
-  // reach one 64-key block past them and then reads zeros, for keys that are
-  // all >= N and masked
-  const __amdgpu_buffer_rsrc_t krs = unit_rsrc(a.k8 + kvu * a.nb * 8192, a.nb * 8192);
-  const __amdgpu_buffer_rsrc_t vrs = unit_rsrc(a.v8 + kvu * a.nb * 8192, a.nb * 8192);
+  const int8_t* const ku = a.k8 + kvu * a.nb * 8192;  // this unit's K8 and V8 blocks
+  const int8_t* const vu = a.v8 + kvu * a.nb * 8192;
   const unsigned lane16 = 16u * (unsigned)tid;
   int kdst[kC], vdst[kC];
 #pragma unroll
@@ -516,20 +525,24 @@ __global__ __launch_bounds__(64 * kW, kBc == 128 ? 2 : 4) void k_attn_prefill16(
   }
   // K_{j+1} and V_{j+1} in flight (registers)
   uint4 kp[kC], vp[kC];
-  auto load_tile = [&](__amdgpu_buffer_rsrc_t r, uint4 (&x)[kC], int j) {
+  // a buffer resource per tile, formed on the scalar unit; what a 128-key tile
+  // reads past the last block are zeros, for keys that are all >= N and masked
+  auto load_tile = [&](const int8_t* unit, uint4 (&x)[kC], int j) {
+    const TileSpan t = tile_span(a.nb, kH, j);
+    const __amdgpu_buffer_rsrc_t r = tile_rsrc(unit + t.offset, kH == 1 ? 8192 : t.bytes);
 #pragma unroll
-    for (int u = 0; u < kC; ++u) x[u] = tile_load(r, lane16 + 16u * kStep * u, j * (8192 * kH));
+    for (int u = 0; u < kC; ++u) x[u] = tile_load(r, lane16 + 16u * kStep * u);
   };
   auto store_tile = [&](int8_t* dst, const int (&d)[kC], const uint4 (&x)[kC]) {
 #pragma unroll
     for (int u = 0; u < kC; ++u) *reinterpret_cast<uint4*>(dst + d[u]) = x[u];
   };
-  load_tile(krs, kp, 0);
-  load_tile(vrs, vp, 0);
+  load_tile(ku, kp, 0);
+  load_tile(vu, vp, 0);
   store_tile(L.k[0], kdst, kp);
   store_tile(L.v[0], vdst, vp);
-  load_tile(krs, kp, min(1, jend));
-  load_tile(vrs, vp, min(1, jend));
+  load_tile(ku, kp, min(1, jend));
+  load_tile(vu, vp, min(1, jend));
 
   // ---- Q_i -> int8 (eq. step1bpq; scale over the 64-row block) ----------
   // lane (n, g), k-step ks: channels 64ks + 16g .. +15 of query qrow
@@ -642,11 +655,11 @@ __global__ __launch_bounds__(64 * kW, kBc == 128 ? 2 : 4) void k_attn_prefill16(
       S[mb] = acc;
     }
     store_tile(L.k[buf ^ 1], kdst, kp);
-    // tile j + 2: buffer loads with the tile offset in a scalar register and
-    // the lane's fixed offset in a vector register (no per-lane address
-    // arithmetic per tile)
+    // tile j + 2: buffer loads with the tile's place in the resource and the
+    // lane's fixed offset in a vector register (no per-lane address arithmetic
+    // per tile)
     const int j2 = min(j + 2, jend);
-    load_tile(krs, kp, j2);
+    load_tile(ku, kp, j2);
     __builtin_amdgcn_s_setprio(0);
     const bool trace_tile = traced && j == a.tr_j;
     if constexpr (kTrace) {
@@ -807,7 +820,7 @@ __global__ __launch_bounds__(64 * kW, kBc == 128 ? 2 : 4) void k_attn_prefill16(
       __builtin_amdgcn_sched_barrier(0);
     }
     store_tile(L.v[buf ^ 1], vdst, vp);
-    load_tile(vrs, vp, j2);
+    load_tile(vu, vp, j2);
     skj = skn;
     svj = svn;
   };
