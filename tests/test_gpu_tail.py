@@ -267,3 +267,22 @@ def test_tail_init_on_views_of_one_buffer(ta, dev):
     torch.cuda.synchronize()
     assert torch.equal(whole.k, parts.k) and torch.equal(whole.v, parts.v)
     assert torch.equal(whole.scale, parts.scale)
+
+
+@pytest.mark.parametrize("N", [64, 64 * 300, 64 * 3 + 1, 64 * 2 + 63])
+def test_tail_init_leaves_nothing_of_the_buffer_before(ta, dev, N):
+    """The slots past the trailing tokens (all of them where N is a multiple of
+    64) are zero whatever they held, and the scales are the largest block scales."""
+    B, Hkv, nt = 2, 3, N % 64
+    _log(f"tail_init over a used buffer N={N}")
+    g = torch.Generator().manual_seed(N)
+    k, v = (torch.randn(B, Hkv, N, 128, generator=g).half().to(dev) for _ in range(2))
+    _, _, sk, sv = ta.turbo_quantize_kv(k, v)
+    t = ta.KVTail(B + 1, Hkv)
+    for x in (t.k, t.v, t.scale):
+        x.fill_(77)
+    ta.turbo_tail_init(k, v, sk, sv, t.narrow(0, B))
+    assert not t.k[:B, :, nt:].any() and not t.v[:B, :, :, nt:].any()
+    assert nt == 0 or (t.k[:B, :, nt - 1].any() and t.v[:B, :, :, nt - 1].any())
+    assert torch.equal(t.scale[:B], torch.stack((sk.amax(-1), sv.amax(-1)), -1))
+    assert all(bool((x[B:] == 77).all()) for x in (t.k, t.v, t.scale))
