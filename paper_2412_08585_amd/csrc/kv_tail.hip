@@ -103,7 +103,8 @@ __global__ __launch_bounds__(256) void k_tail_init(TailInitArgs a) {
   m = block_max(m, red);
   if (tid == 0) a.tscale[2 * u + isv] = m;
   unsigned w[8];
-  tail_codes(raw, univ_inv(m), w);
+  // (rows past the last token hold zeros for any scale, whose inverse may be inf)
+  tail_codes(raw, t < nt ? univ_inv(m) : 0.0f, w);
   if (!isv) {  // token-major
     uint4* dst = reinterpret_cast<uint4*>(a.tk + (u * 64 + t) * 128 + c0);
     dst[0] = make_uint4(w[0], w[1], w[2], w[3]);

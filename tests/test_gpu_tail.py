@@ -286,3 +286,15 @@ def test_tail_init_leaves_nothing_of_the_buffer_before(ta, dev, N):
     assert nt == 0 or (t.k[:B, :, nt - 1].any() and t.v[:B, :, :, nt - 1].any())
     assert torch.equal(t.scale[:B], torch.stack((sk.amax(-1), sv.amax(-1)), -1))
     assert all(bool((x[B:] == 77).all()) for x in (t.k, t.v, t.scale))
+
+
+def test_tail_init_unused_rows_with_a_tiny_scale(ta, dev):
+    """A scale below 2^-128, whose inverse is infinite: rows past the last token
+    are zero all the same."""
+    B, Hkv, N = 1, 2, 64 + 5
+    g = torch.Generator().manual_seed(3)
+    k, v = (torch.randn(B, Hkv, N, 128, generator=g).half().to(dev) for _ in range(2))
+    s = torch.full((B, Hkv, 2), 1e-42, device=dev)
+    t = ta.KVTail(B, Hkv)
+    ta.turbo_tail_init(k, v, s, s, t)
+    assert not t.k[:, :, 5:].any() and not t.v[:, :, :, 5:].any()
