@@ -111,6 +111,26 @@ __device__ __forceinline__ DecodeSeq decode_seq(const DecodeArgs& a, int b) {
   return q;
 }
 
+// The chunk s of (sequence b, KV head kh) that a work-group takes.  A sequence's
+// chunks are rotated by b: work-groups go to the eight XCDs, and within one to its
+// shader engines and CUs, in turn, so that with four chunks per head in order the
+// first chunk of every head would fall on the same two XCDs.  Where the tables are
+// wider than the sequences need, the first is the only one that is not empty: 64
+// sequences of 2000 tokens in tables of 512 groups, 64/8 heads, 104 us in order,
+// 63 rotated; 256 of 1000, 32/8 heads, 125 / 57.  By sequence, not by head, since the
+// heads share the chunk's table entries (by head: 32k-token batches 1.5 % slower).
+// The digits to the base 4 (2) of b are summed, so that the rotation does not repeat
+// in step with a power of two.
+__device__ __forceinline__ void decode_place(const DecodeArgs& a, int& b, int& kh, int& s) {
+  const unsigned n = a.nsplit, u = blockIdx.x / n, j = blockIdx.x - u * n;
+  b = (int)(u / (unsigned)a.Hkv);
+  kh = (int)u - b * a.Hkv;
+  const unsigned x = (unsigned)b;
+  const unsigned rot = n % 4 == 0 ? x + (x >> 2) + (x >> 4) + (x >> 6)
+                       : n % 2 == 0 ? (unsigned)__popc(x) : 0u;  // odd: no pattern to break
+  s = (int)((j + rot) % n);
+}
+
 // o = 0 and lse = -inf for the G rows of (b, kh): a sequence with nothing to
 // attend.
 __device__ void decode_write_empty(const DecodeArgs& a, int b, int kh) {
@@ -1132,9 +1152,8 @@ __global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_d
   constexpr int LPR = 64 / GP;
   constexpr int kRows = Slice<GP, W>::kRows, kCh = Slice<GP, W>::kCh;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int s = blockIdx.x % a.nsplit;
-  const int kh = (blockIdx.x / a.nsplit) % a.Hkv;
-  const int b = blockIdx.x / (a.nsplit * a.Hkv);
+  int b, kh, s;
+  decode_place(a, b, kh, s);
   const int lane = threadIdx.x & 63;
   const int rr = lane / LPR, cc = lane % LPR;
   const int G = a.G;
@@ -1213,9 +1232,8 @@ __global__ __launch_bounds__(64, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decod
     return;
   }
   __shared__ DecodeLds<GP> L;
-  const int s = blockIdx.x % a.nsplit;
-  const int kh = (blockIdx.x / a.nsplit) % a.Hkv;
-  const int b = blockIdx.x / (a.nsplit * a.Hkv);
+  int b, kh, s;
+  decode_place(a, b, kh, s);
   constexpr int LPR = 64 / GP;
   const int lane = threadIdx.x & 63;
   if (lane < 8) L.lut[lane] = kLut[lane];

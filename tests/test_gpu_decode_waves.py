@@ -102,3 +102,42 @@ def test_decode_waves_trace_the_same_integers(ta, dev, G):
             assert np.any(t["pvacc"])
             for name in t:
                 assert np.array_equal(t[name], want[name]), (B, name)
+
+
+@pytest.mark.parametrize("G,B", [(1, 3), (4, 21), (8, 9)])
+def test_decode_tables_wider_than_the_sequences(ta, dev, G, B):
+    """The work-groups of a chunk number are rotated by the sequence, over as many
+    chunks as the table's width asks for (one, two, three and four here, and five
+    and six by an explicit split); sequences of every number of chunks, and empty
+    ones, give the bits that each gives alone in a table of its own width."""
+    print(f"decode wide tables G={G} B={B}", flush=True)
+    Hkv, bits = 2, [4, 2]
+    groups = [(0, 1, 3, 9, 20, 31)[i % 6] + i // 6 for i in range(B)]
+    total = sum(groups)
+    k, v = _rand((1, Hkv, 64 * total, 128), 80 + G), _rand((1, Hkv, 64 * total, 128), 90 + G)
+    q = _rand((B, G * Hkv, 128), 100 + G).to(dev)
+    cache = ta.PagedKVCache(4 * total, total, bits, dev)
+    gall = torch.randperm(total, generator=torch.Generator().manual_seed(B)).int()
+    ball = (4 * gall[:, None] + torch.arange(4)).int()
+    ta.turbo_quantize_kv(k.to(dev), v.to(dev), cache, ball.reshape(1, -1).to(dev),
+                         gall[None].to(dev))
+
+    def run(rows, width, split):
+        gt = torch.full((len(rows), width), -1, dtype=torch.int32)
+        bt = torch.full((len(rows), width, 4), -1, dtype=torch.int32)
+        for i, r in enumerate(rows):
+            at, n = sum(groups[:r]), groups[r]
+            gt[i, :n], bt[i, :n] = gall[at:at + n], ball[at:at + n]
+        sl = torch.tensor([64 * groups[r] for r in rows], dtype=torch.int32, device=dev)
+        o, lse = ta.turbo_attn_decode(q[rows], cache, sl, bt.view(len(rows), -1).to(dev),
+                                      gt.to(dev), SM, split, return_lse=True)
+        torch.cuda.synchronize()
+        return o, lse
+
+    for split, widths in ((0, (max(groups), 40, 70, 400)), (8, (40, 45))):
+        alone = [run([r], max(groups[r], 1), split) for r in range(B)]
+        for width in widths:
+            o, lse = run(list(range(B)), width, split)
+            for r in range(B):
+                assert torch.equal(_bits(o[r]), _bits(alone[r][0][0])), (split, width, r)
+                assert torch.equal(_bits(lse[r]), _bits(alone[r][1][0])), (split, width, r)
