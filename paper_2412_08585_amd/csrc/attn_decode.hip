@@ -894,14 +894,15 @@ struct Slice {
   static constexpr int kCh = GP >= W ? 2 : 1;
 };
 
-template <int GP, int BITS, int W, bool kTrace>
+// E of the work-group's W waves take part: all of them, or the first alone.
+template <int GP, int BITS, int W, int E, bool kTrace>
 __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>& LW, int w, int b,
                                             int kh, int g0, int g1, int head_off, float& mrow,
                                             float& lpart, float& beta,
-                                            float (&O)[Slice<GP, W>::kRows][Slice<GP, W>::kCh],
+                                            float (&O)[Slice<GP, E>::kRows][Slice<GP, E>::kCh],
                                             int trow) {
   constexpr int LPR = 64 / GP;
-  constexpr int kRows = Slice<GP, W>::kRows, kCh = Slice<GP, W>::kCh;
+  constexpr int kRows = Slice<GP, E>::kRows, kCh = Slice<GP, E>::kCh;
   CoopWave<GP>& L = LW.wave[w];
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g4 = lane >> 4;
@@ -913,11 +914,18 @@ __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>&
   const int* bt = a.block_table + (long)b * 4 * a.max_groups;
   const int* gt = a.group_table + (long)b * a.max_groups;
 
+  // a lone wave has only its own LDS accesses to order
+  auto coop_sync = [] {
+    if constexpr (E > 1)
+      __syncthreads();
+    else
+      wave_sync();
+  };
   GroupTab T;
   GroupK<BITS> K;
-  load_tab<W>(a, kh, bt, gt, g0 + w, g1, T);
+  load_tab<E>(a, kh, bt, gt, g0 + w, g1, T);
   auto next_k = [&](int st) {  // the wave's group of step st
-    if (st != 0 && (st & 63) == 0) load_tab<W>(a, kh, bt, gt, g0 + w + W * st, g1, T);
+    if (st != 0 && (st & 63) == 0) load_tab<E>(a, kh, bt, gt, g0 + w + E * st, g1, T);
     load_k<BITS>(a, kh, head_off, T, st & 63, K);
   };
   next_k(0);  // on its way while the query is quantized
@@ -928,9 +936,9 @@ __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>&
   Wq.load(L.qbuf);
   wave_sync();  // orow takes qbuf's place
 
-  const int nst = ceil_div(g1 - g0, W);  // work-group uniform
+  const int nst = ceil_div(g1 - g0, E);  // work-group uniform
   for (int st = 0; st < nst; ++st) {
-    const int g = g0 + w + W * st;
+    const int g = g0 + w + E * st;
     const bool ok = K.ok;
     tab_scales<BITS>(T, st & 63, K);  // before next_k moves the table on
     const float skg = K.skg, svg = K.svg;
@@ -988,29 +996,36 @@ __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>&
     } else {
       next_k(st + 1);
     }
-    if (cc == 0) LW.gmax[rr][w] = smax;
-    if (lane == 0) LW.ok[w] = ok;
-    __syncthreads();
+    if constexpr (E > 1) {
+      if (cc == 0) LW.gmax[rr][w] = smax;
+      if (lane == 0) LW.ok[w] = ok;
+    }
+    coop_sync();
 
     // ---- running maximum and rescale factors of the step's groups ---------
-    float gm[W], f[W], mnew = mrow;
+    float gm[E], f[E], mnew = mrow;
+    unsigned okm;
+    if constexpr (E == 1) {
+      gm[0] = smax;
+      okm = ok;
+    } else {
 #pragma unroll
-    for (int i = 0; i < W; i += 2) {
-      const float2 t = *reinterpret_cast<const float2*>(&LW.gmax[rr][i]);
-      gm[i] = t.x; gm[i + 1] = t.y;
+      for (int i = 0; i < E; i += 2) {
+        const float2 t = *reinterpret_cast<const float2*>(&LW.gmax[rr][i]);
+        gm[i] = t.x; gm[i + (E > 1)] = t.y;
+      }
+      okm = (unsigned)__builtin_amdgcn_ballot_w64(LW.ok[lane & (E - 1)] != 0) & ((1u << E) - 1);
     }
-    const unsigned okm =
-        (unsigned)__builtin_amdgcn_ballot_w64(LW.ok[lane & (W - 1)] != 0) & ((1u << W) - 1);
     float top = gm[0];
 #pragma unroll
-    for (int i = 1; i < W; ++i) top = fmaxf(top, gm[i]);
+    for (int i = 1; i < E; ++i) top = fmaxf(top, gm[i]);
     // no row moves its maximum in this step: every factor is 1 (e^0)
     const bool moved = __builtin_amdgcn_ballot_w64(top > mrow) != 0;
     if (moved) {
-      // the W factors side by side (no branch, one table latency for all)
+      // the E factors side by side (no branch, one table latency for all)
       float m = mrow;
 #pragma unroll
-      for (int i = 0; i < W; ++i) {
+      for (int i = 0; i < E; ++i) {
         const float mi = fmaxf(m, gm[i]);
         f[i] = sas_y(mi - m, LW.lut);  // 0 when m = -inf
         f[i] = mi > m ? f[i] : 1.0f;
@@ -1067,7 +1082,7 @@ __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>&
         L.vsz[32 + (lane >> 1)] = cv.vz4;
       }
     }
-    __syncthreads();
+    coop_sync();
 
     // ---- the step's groups, in order ---------------------------------------
     // O += g * (s * sum P*code + z * sum P) of group i, g = s_P s_V / beta
@@ -1105,13 +1120,13 @@ __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>&
           // exact int32 PV of Algorithm 2 (every factor fits 24 bits)
           const int pv = __mul24(sc[c2], acc[c2]) + __mul24(zc[c2], psum);
           O[r][c2] = __builtin_fmaf(gr, (float)pv, O[r][c2]);
-          if (kTrace && trow == row0 + r && g0 + W * st + i == a.tr_g)
+          if (kTrace && trow == row0 + r && g0 + E * st + i == a.tr_g)
             reinterpret_cast<int*>(a.trace + TURBO_TRACE_PV)[ch + c2] = pv;
         }
       }
     };
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
+    for (int i = 0; i < E; ++i) {
       if (!((okm >> i) & 1u)) continue;  // work-group uniform
       const float alpha = moved ? f[i] : 1.0f;
       lpart = alpha * lpart + LW.wave[i].rs[lane];
@@ -1139,32 +1154,16 @@ __device__ __forceinline__ void decode_coop(const DecodeArgs& a, CoopLds<GP, W>&
 template <int GP, int W, bool kTrace>
 __device__ void decode_tail_body(const DecodeArgs& a, int bx);  // kv_tail.hip
 
-// W waves per (b, KV head, chunk of groups).
-template <int GP, int W, bool kTrace>
-__global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decode_coop(
-    DecodeArgs a) {
-  const int nmain = a.B * a.Hkv * a.nsplit;
-  if ((int)blockIdx.x >= nmain) {
-    decode_tail_body<GP, W, kTrace>(a, (int)blockIdx.x - nmain);
-    return;
-  }
-  __shared__ CoopLds<GP, W> LW;
+// One chunk, groups g0 .. g1 - 1 of (b, kh), by E of the work-group's waves.
+template <int GP, int W, int E, bool kTrace>
+__device__ __forceinline__ void coop_chunk(const DecodeArgs& a, CoopLds<GP, W>& LW,
+                                           const DecodeSeq& sq_, int w, int b, int kh, int s, int g0,
+                                           int g1) {
   constexpr int LPR = 64 / GP;
-  constexpr int kRows = Slice<GP, W>::kRows, kCh = Slice<GP, W>::kCh;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int b, kh, s;
-  decode_place(a, b, kh, s);
+  constexpr int kRows = Slice<GP, E>::kRows, kCh = Slice<GP, E>::kCh;
   const int lane = threadIdx.x & 63;
   const int rr = lane / LPR, cc = lane % LPR;
   const int G = a.G;
-  const DecodeSeq sq_ = decode_seq(a, b);
-  const int g0 = s * sq_.split;
-  const int g1 = min(sq_.ng, g0 + sq_.split);
-  if (g1 <= g0) {  // no group of this sequence in the chunk
-    if (s == 0 && sq_.nparts == 0) decode_write_empty(a, b, kh);
-    return;
-  }
-  if (threadIdx.x < 8) LW.lut[lane] = kLut[lane];  // read behind the first step's barrier
   const int bits = ((a.int2_mask >> kh) & 1ull) ? 2 : 4;
   const int head_off = 512 * (4 * kh - 2 * __popcll(a.int2_mask & ((1ull << kh) - 1ull)));
   // traced row of this work-group (-1: none), whose chunk holds group tr_g
@@ -1173,9 +1172,9 @@ __global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_d
   float O[kRows][kCh] = {};
   float mrow = -INFINITY, lpart = 0.0f, beta = 1.0f;
   if (bits == 4)
-    decode_coop<GP, 4, W, kTrace>(a, LW, w, b, kh, g0, g1, head_off, mrow, lpart, beta, O, trow);
+    decode_coop<GP, 4, W, E, kTrace>(a, LW, w, b, kh, g0, g1, head_off, mrow, lpart, beta, O, trow);
   else
-    decode_coop<GP, 2, W, kTrace>(a, LW, w, b, kh, g0, g1, head_off, mrow, lpart, beta, O, trow);
+    decode_coop<GP, 2, W, E, kTrace>(a, LW, w, b, kh, g0, g1, head_off, mrow, lpart, beta, O, trow);
 
   // every wave holds m, l and beta of all rows and its slice of O
   const float l = row_sum<LPR>(lpart);
@@ -1217,6 +1216,38 @@ __global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_d
       a.lse[bh] = mrow + logf(l);
     }
   }
+}
+
+// W waves per (b, KV head, chunk of groups).
+template <int GP, int W, bool kTrace>
+__global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decode_coop(
+    DecodeArgs a) {
+  const int nmain = a.B * a.Hkv * a.nsplit;
+  if ((int)blockIdx.x >= nmain) {
+    decode_tail_body<GP, W, kTrace>(a, (int)blockIdx.x - nmain);
+    return;
+  }
+  __shared__ CoopLds<GP, W> LW;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int b, kh, s;
+  decode_place(a, b, kh, s);
+  const DecodeSeq sq_ = decode_seq(a, b);
+  const int g0 = s * sq_.split;
+  const int g1 = min(sq_.ng, g0 + sq_.split);
+  if (g1 <= g0) {  // no group of this sequence in the chunk
+    if (s == 0 && sq_.nparts == 0) decode_write_empty(a, b, kh);
+    return;
+  }
+  if (threadIdx.x < 8) LW.lut[threadIdx.x] = kLut[threadIdx.x];  // read behind the first step's barrier
+  // A chunk of one group is left to the first wave.  The others end here (a wave
+  // that has ended no longer counts at a barrier): one sequence of 64 tokens in a
+  // table of 512 groups, W = 8, 8.1 us with all of them, 6.9 so (GP = 4); 256 such
+  // sequences, GP = 8, 22.8 -> 19.8.  With sixteen rows it gains nothing.
+  if (GP <= 8 && g1 - g0 == 1) {
+    if (w == 0) coop_chunk<GP, W, 1, kTrace>(a, LW, sq_, w, b, kh, s, g0, g1);
+    return;
+  }
+  coop_chunk<GP, W, W, kTrace>(a, LW, sq_, w, b, kh, s, g0, g1);
 }
 
 // kTrace = true only for the test hook that also stores one group's integers
@@ -1363,13 +1394,17 @@ __global__ __launch_bounds__(64) void k_decode_combine(DecodeArgs a) {
 template <int W, bool kTrace>
 static void launch_decode(const DecodeArgs& a, int total, hipStream_t stream) {
   const dim3 grid(total), block(64 * W);
-  if constexpr (W == 1) {  // at most four rows
+  if constexpr (W == 1) {
     if (a.G <= 1)
       hipLaunchKernelGGL((k_attn_decode<1, kTrace>), grid, block, 0, stream, a);
     else if (a.G <= 2)
       hipLaunchKernelGGL((k_attn_decode<2, kTrace>), grid, block, 0, stream, a);
-    else
+    else if (a.G <= 4)
       hipLaunchKernelGGL((k_attn_decode<4, kTrace>), grid, block, 0, stream, a);
+    else if (a.G <= 8)
+      hipLaunchKernelGGL((k_attn_decode<8, kTrace>), grid, block, 0, stream, a);
+    else
+      hipLaunchKernelGGL((k_attn_decode<16, kTrace>), grid, block, 0, stream, a);
   } else if (a.G <= 1) {
     hipLaunchKernelGGL((k_attn_decode_coop<1, W, kTrace>), grid, block, 0, stream, a);
   } else if (a.G <= 2) {
@@ -1383,36 +1418,52 @@ static void launch_decode(const DecodeArgs& a, int total, hipStream_t stream) {
   }
 }
 
-// Waves per work-group (W).  One wave takes about 1.3 us per group (GP = 4)
-// whatever the load, so a launch of few chunks is bound by the chain of groups
-// of its longest one; W waves cut the chain W-fold, at about 2.3 (W = 4) and
-// 3.3 us (W = 8) per step of W groups, since they share the CU's LDS.  A launch
-// that fills the chip anyway is bound by the sum of its work, where W > 1 pays
-// for W prologues and the exchanges.  So W is the most for which every chunk is
-// resident at once: three waves per SIMD (3072) up to eight rows, two with
-// sixteen, one work-group of eight waves per CU.  Measured, us per decoding step
-// (int4 or mixed, equal sequences), W = 1 / 2 / 4 / 8.  4000 cached tokens in two
-// chunks, GP = 4: 64 chunks 54 / 43 / 31 / 26, 256: 56 / 45 / 34 / 33, 512: 60 /
-// 50 / 40 / 55, 768: 66 / 55 / 49 / 77, 1024: 71 / 62 / 72 / 99, 1536: 85 / 81 /
-// 90 / 143, 2560: 134 / 138 / 145 / 230.  16384 tokens in four, GP = 1: 768: 96 /
-// 79 / 74 / 101, 1024: 98 / 93 / 112 / 132, 1280: 116 / 115 / 123 / 163, 1792:
-// 155 / 189 / 173 / 219; GP = 8: 1024: - / 109 / 127 / 156.  More than four rows
-// in one wave spill (GP = 8: 78 at 512 chunks of 4000 tokens against 56 / 44 / 59
-// for W = 2 / 4 / 8, 497 at 8192 chunks of 8000 against 389), so they take two
-// waves at least.  With them, chunks of 48 groups and more take four waves also
-// where only three quarters are resident at once (all, with sixteen rows: half):
-// 16 % behind two waves if the sequences are equally long, 16 % ahead if they are
-// not (32 sequences of 256 to 16383 tokens, GP = 8: - / 92 / 77 / 92; 2048 chunks
-// of 16000 tokens, GP = 16: - / 337 / 294 / 352).  All with the scales read
-// ahead of the codes (load_k): W > 1 is 1-6 % faster since, the order the same.
+// Waves per work-group (W).  One wave takes 1.2 (GP = 1) to 2.3 us (GP = 16) per
+// group whatever the load, so a launch of few chunks is bound by the chain of groups
+// of its longest one; W waves cut the chain W-fold, at about 2.3 (W = 4) and 3.3 us
+// (W = 8) per step of W groups.  A launch that fills the chip is bound by the sum of
+// its work, where W > 1 pays for W prologues and the exchanges.  So W is the most
+// waves with which every chunk is resident at once, where the chunks are long enough
+// to give each wave work, and one wave otherwise.  Resident chunks by registers and
+// LDS, W = 1 / 2 / 4 / 8: 3072 / 1536 / 768 / 256 up to four rows, 2304 / 1536 / 768 /
+// 256 with eight, 1536 / 1024 / 512 / 256 with sixteen.
+//
+// us of a launch by chunks (all of one length, mixed widths), W = 1 / 2 / 4 / 8:
+//   GP = 4, 2 groups: 512: 8.4 / 8.2 / 8.5, 1024: 9.2 / 9.3 / 13.0; 4 groups: 512: 11.4 /
+//   10.5 / 9.1, 1024: 12.7 / 12.5 / 16.1, 1280: 14.1 / 14.5 / 17.8; 8 groups: 256: 16.4 /
+//   13.1 / 10.7 / 10.0, 512: 17.6 / 15.1 / 12.4 / 17.3, 768: 18.5 / 16.3 / 15.9, 1536:
+//   22.9 / 22.0 / 28.1, 2048: 25.0 / 33.3 / 38.1.  GP = 1 and 2 cross at the same sizes.
+//   GP = 8, 2 groups: 1024: 11.7 / 10.8 / 15.2, 1536: 13.0 / 13.1 / 19.5; 8 groups: 768:
+//   26.5 / 19.2 / 17.8, 1536: 31.3 / 25.1 / 31.7, 2048: 35.1 / 38.9 / 42.1; 48 groups:
+//   2048: 169 / 166 / 164.  Past what one wave keeps resident two are ahead again: 2560
+//   of 8 groups 59.0 / 45.9 / 51.7, of 2 22.5 / 22.3; 8192 of 8 130 / 119, of 4 76 / 78.
+//   GP = 16, 8 groups: 512: 27.9 / 22.3 / 16.7, 1024: 29.6 / 25.3 / 31.1, 1536: 35.1 /
+//   44.3 / 44.6; 48 groups: 1536: 164 / 196 / 172, 2048: 276 / 257 / 214, 2560: 304 / 280 /
+//   267, 3072: 310 / 355 / 320.
+// With eight rows and 769 to 1024 long chunks, a quarter of them not resident with four
+// waves, it is raggedness that decides, which the host does not see: 1024 chunks of up
+// to 64 groups 174 / 106 / 125 where all are equally long, 155 / 89 / 61 where they are not
+// (32 sequences of 256 to 16383 tokens).  Four waves are taken: ahead of one in both.
+//
+// The number of chunks is that of the grid, from the width of the tables.  Shorter
+// sequences leave some of them empty, and then fewer waves are taken than would be
+// best: 64 sequences of 2000 tokens, 32/8 heads, 53 us in tables of 512 groups, 31 in
+// their own.  The buffer's work-groups are not counted.
 static int decode_waves(const DecodeArgs& a) {
   const long units = (long)a.B * a.Hkv * a.nsplit;
-  const long waves = a.G > 8 ? 2048 : 3072;
   const int len = ceil_div(a.max_groups, a.nsplit);  // groups of the longest chunk, or one more
   if (units <= 256 && len >= 8) return 8;
-  if (4 * units <= waves && len >= 4) return 4;
-  if (a.G > 4) return len >= 48 && units <= (a.G > 8 ? 2048 : 1024) ? 4 : 2;
-  return 2 * units <= waves && len >= 2 ? 2 : 1;
+  if (units <= 512 && len >= 3) return 4;
+  if (a.G <= 4) {
+    if (units <= 768 && len >= 8) return 4;
+    return units <= 1536 && len >= (units <= 512 ? 2 : units <= 1024 ? 4 : 8) ? 2 : 1;
+  }
+  if (a.G <= 8) {
+    if ((units <= 768 && len >= 8) || (units <= 1024 && len >= 48)) return 4;
+    return len >= (units <= 1024 ? 2 : units <= 1536 ? 4 : units <= 2304 ? 32 : 6) ? 2 : 1;
+  }
+  if (units <= 1024) return len >= 2 ? 2 : 1;
+  return units > 1536 && units <= 2560 && len >= 16 ? 4 : 1;
 }
 
 hipError_t launch_attn_decode(const DecodeArgs& a, hipStream_t stream) {

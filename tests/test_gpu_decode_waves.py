@@ -1,10 +1,12 @@
 """Decode with one, two, four and eight waves per chunk: the waves share the
 groups of a chunk, and the result is that of one wave, bit for bit.
 
-The number of waves follows the number of chunks in the launch, so one sequence
-is decoded alone and repeated 160, 500 and 1000 times (two KV heads, one chunk
-each: 2, 320, 1000 and 2000 chunks); its rows must have the same bits each time,
-and the lone one is checked against the CPU oracle.
+The number of waves follows the number of chunks in the launch and their length,
+so one sequence is decoded alone and repeated 160, 500 and 1000 times (two KV
+heads, one chunk each: 2, 320, 1000 and 2000 chunks); its rows must have the same
+bits each time, and the lone one is checked against the CPU oracle.  Of 9 groups
+that is eight, four, two and one wave for every number of rows; of 64 with eight
+rows eight, four, four and two, with sixteen eight, four, two and four.
 """
 import numpy as np
 import pytest
@@ -38,8 +40,11 @@ def _bits(t):
 
 
 # groups: below, at and past the steps of 2, 4 and 8 groups; one group; past the
-# 64 table entries a lane holds at a time (64 steps of 8 groups)
-CASES = [(G, ng) for G in (1, 2, 4, 8, 16) for ng in (1, 9, 31)] + [(3, 16), (5, 22), (2, 515)]
+# 64 table entries a lane holds at a time (515: 64 steps of 8 groups; 130 with one
+# row: twice with one wave, once with two); the lengths past which long chunks take
+# other numbers of waves
+CASES = [(G, ng) for G in (1, 2, 4, 8, 16) for ng in (1, 9, 31)] + [
+    (3, 16), (5, 22), (2, 515), (1, 130), (8, 64), (16, 64)]
 
 
 @pytest.mark.parametrize("G,ng", CASES)
