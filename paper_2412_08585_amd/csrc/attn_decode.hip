@@ -111,24 +111,38 @@ __device__ __forceinline__ DecodeSeq decode_seq(const DecodeArgs& a, int b) {
   return q;
 }
 
-// The chunk s of (sequence b, KV head kh) that a work-group takes.  A sequence's
-// chunks are rotated by b: work-groups go to the eight XCDs, and within one to its
-// shader engines and CUs, in turn, so that with four chunks per head in order the
-// first chunk of every head would fall on the same two XCDs.  Where the tables are
-// wider than the sequences need, the first is the only one that is not empty: 64
-// sequences of 2000 tokens in tables of 512 groups, 64/8 heads, 104 us in order,
-// 63 rotated; 256 of 1000, 32/8 heads, 125 / 57.  By sequence, not by head, since the
-// heads share the chunk's table entries (by head: 32k-token batches 1.5 % slower).
-// The digits to the base 4 (2) of b are summed, so that the rotation does not repeat
-// in step with a power of two.
-__device__ __forceinline__ void decode_place(const DecodeArgs& a, int& b, int& kh, int& s) {
-  const unsigned n = a.nsplit, u = blockIdx.x / n, j = blockIdx.x - u * n;
+// The chunk s of (sequence b, KV head kh) that a work-group takes.  Work-groups go
+// to the eight XCDs, and within one to its shader engines and CUs, in turn: with two,
+// four, eight .. chunks per head in order, the first chunks of all heads fall on a
+// few of them.  Where the tables are wider than the sequences need, those are the
+// only ones that are not empty.  So the chunks of a sequence that leaves some empty
+// are rotated by b: 64 sequences of 2000 tokens in tables of 512 groups, 64/8 heads,
+// 104 us in order, 62 rotated; 256 of 1000, 32/8 heads, 125 / 57; 64 of 1000 in chunks
+// of 16 groups 204 / 39; ragged batches gain 3 to 10 %.  By sequence, not by head,
+// since the heads share the chunk's table entries.  The digits to the base 4 (2) of b
+// are summed, so that the rotation does not repeat in step with a power of two.
+// Sequences that fill their chunks stay in order: rotated, equal batches lost up to
+// 5 %, and so did all with 6, 10, .. chunks.
+__device__ __forceinline__ DecodeSeq decode_place(const DecodeArgs& a, int& b, int& kh, int& s) {
+  const unsigned n = a.nsplit;
+  unsigned u = blockIdx.x, j = 0;
+  if ((n & (n - 1)) == 0) {  // mostly one, two or four: no division
+    u >>= __builtin_ctz(n);
+    j = blockIdx.x & (n - 1);
+  } else {
+    u /= n;
+    j = blockIdx.x - u * n;
+  }
   b = (int)(u / (unsigned)a.Hkv);
   kh = (int)u - b * a.Hkv;
-  const unsigned x = (unsigned)b;
-  const unsigned rot = n % 4 == 0 ? x + (x >> 2) + (x >> 4) + (x >> 6)
-                       : n % 2 == 0 ? (unsigned)__popc(x) : 0u;  // odd: no pattern to break
-  s = (int)((j + rot) % n);
+  const DecodeSeq q = decode_seq(a, b);
+  if (q.nchunk < (int)n && (n == 2 || n % 4 == 0)) {
+    const unsigned x = (unsigned)b;
+    j += n == 2 ? (unsigned)__builtin_popcount(x) : x + (x >> 2) + (x >> 4) + (x >> 6);
+    j = (n & (n - 1)) == 0 ? j & (n - 1) : j % n;
+  }
+  s = (int)j;
+  return q;
 }
 
 // o = 0 and lse = -inf for the G rows of (b, kh): a sequence with nothing to
@@ -1230,8 +1244,7 @@ __global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_d
   __shared__ CoopLds<GP, W> LW;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int b, kh, s;
-  decode_place(a, b, kh, s);
-  const DecodeSeq sq_ = decode_seq(a, b);
+  const DecodeSeq sq_ = decode_place(a, b, kh, s);
   const int g0 = s * sq_.split;
   const int g1 = min(sq_.ng, g0 + sq_.split);
   if (g1 <= g0) {  // no group of this sequence in the chunk
@@ -1241,9 +1254,9 @@ __global__ __launch_bounds__(64 * W, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_d
   if (threadIdx.x < 8) LW.lut[threadIdx.x] = kLut[threadIdx.x];  // read behind the first step's barrier
   // A chunk of one group is left to the first wave.  The others end here (a wave
   // that has ended no longer counts at a barrier): one sequence of 64 tokens in a
-  // table of 512 groups, W = 8, 8.1 us with all of them, 6.9 so (GP = 4); 256 such
-  // sequences, GP = 8, 22.8 -> 19.8.  With sixteen rows it gains nothing.
-  if (GP <= 8 && g1 - g0 == 1) {
+  // table of 512 groups, W = 8, 8.1 us with all of them, 6.9 so (GP = 4).  With eight
+  // rows the second path costs long chunks 3 %, with sixteen it gains nothing.
+  if (GP <= 4 && g1 - g0 == 1) {
     if (w == 0) coop_chunk<GP, W, 1, kTrace>(a, LW, sq_, w, b, kh, s, g0, g1);
     return;
   }
@@ -1264,14 +1277,13 @@ __global__ __launch_bounds__(64, (GP <= 8 && !kTrace) ? 3 : 2) void k_attn_decod
   }
   __shared__ DecodeLds<GP> L;
   int b, kh, s;
-  decode_place(a, b, kh, s);
+  const DecodeSeq sq_ = decode_place(a, b, kh, s);
   constexpr int LPR = 64 / GP;
   const int lane = threadIdx.x & 63;
   if (lane < 8) L.lut[lane] = kLut[lane];
   const int rr = lane / LPR, cc = lane % LPR;
   const int G = a.G;
 
-  const DecodeSeq sq_ = decode_seq(a, b);
   const int g0 = s * sq_.split;
   const int g1 = min(sq_.ng, g0 + sq_.split);
   if (g1 <= g0) {  // no group of this sequence in the chunk
@@ -1423,12 +1435,12 @@ static void launch_decode(const DecodeArgs& a, int total, hipStream_t stream) {
 // of its longest one; W waves cut the chain W-fold, at about 2.3 (W = 4) and 3.3 us
 // (W = 8) per step of W groups.  A launch that fills the chip is bound by the sum of
 // its work, where W > 1 pays for W prologues and the exchanges.  So W is the most
-// waves with which every chunk is resident at once, where the chunks are long enough
-// to give each wave work, and one wave otherwise.  Resident chunks by registers and
-// LDS, W = 1 / 2 / 4 / 8: 3072 / 1536 / 768 / 256 up to four rows, 2304 / 1536 / 768 /
-// 256 with eight, 1536 / 1024 / 512 / 256 with sixteen.
+// waves with which every work-group is resident at once, where the chunks are long
+// enough to give each wave work, and one wave otherwise.  Resident work-groups by
+// registers and LDS, W = 1 / 2 / 4 / 8: 3072 / 1536 / 768 / 256 up to four rows, 2304 /
+// 1536 / 768 / 256 with eight, 1536 / 1024 / 512 / 256 with sixteen.
 //
-// us of a launch by chunks (all of one length, mixed widths), W = 1 / 2 / 4 / 8:
+// us of a launch by chunks (all of one length, int4 and int2 heads), W = 1 / 2 / 4 / 8:
 //   GP = 4, 2 groups: 512: 8.4 / 8.2 / 8.5, 1024: 9.2 / 9.3 / 13.0; 4 groups: 512: 11.4 /
 //   10.5 / 9.1, 1024: 12.7 / 12.5 / 16.1, 1280: 14.1 / 14.5 / 17.8; 8 groups: 256: 16.4 /
 //   13.1 / 10.7 / 10.0, 512: 17.6 / 15.1 / 12.4 / 17.3, 768: 18.5 / 16.3 / 15.9, 1536:
@@ -1440,30 +1452,49 @@ static void launch_decode(const DecodeArgs& a, int total, hipStream_t stream) {
 //   GP = 16, 8 groups: 512: 27.9 / 22.3 / 16.7, 1024: 29.6 / 25.3 / 31.1, 1536: 35.1 /
 //   44.3 / 44.6; 48 groups: 1536: 164 / 196 / 172, 2048: 276 / 257 / 214, 2560: 304 / 280 /
 //   267, 3072: 310 / 355 / 320.
-// With eight rows and 769 to 1024 long chunks, a quarter of them not resident with four
-// waves, it is raggedness that decides, which the host does not see: 1024 chunks of up
-// to 64 groups 174 / 106 / 125 where all are equally long, 155 / 89 / 61 where they are not
-// (32 sequences of 256 to 16383 tokens).  Four waves are taken: ahead of one in both.
+// With a buffer its work-groups come last, one per (sequence, KV head), and take their
+// rows a wave at a time.  They count beside short chunks, half beside chunks of 12 to
+// 15 groups; longer ones outlast them.  One chunk each: GP = 4, 8 groups: 64: 19.3 /
+// 16.0 / 13.5 / 12.6, 256: 20.3 / 17.3 / 14.6 / 17.7, 512: 22.6 / 20.6 / 20.7, 768: 24.1 /
+// 23.2 / 27.7, 1024: 26.5 / 27.6 / 34.3; 16 groups: 512: 34.4 / 29.2 / 25.4, 1024: 41.1 /
+// 39.6 / 43.7, 1536: 49.6 / 48.6.  With more rows they are the longest part, and more
+// waves shorten it: GP = 8, 4 groups: 768: 27.3 / 24.0 / 28.4, 1024: 29.2 / 30.5, 1536:
+// 42.6 / 39.8, 3072: 70.2 / 67.7; GP = 16: 512: 36.5 / 29.2 / 29.9, 1024: 54.4 / 52.8 /
+// 50.8, 1536: 61.8 / 67.5, 2048: 90.5 / 84.7.
 //
-// The number of chunks is that of the grid, from the width of the tables.  Shorter
-// sequences leave some of them empty, and then fewer waves are taken than would be
-// best: 64 sequences of 2000 tokens, 32/8 heads, 53 us in tables of 512 groups, 31 in
-// their own.  The buffer's work-groups are not counted.
+// The host sees neither lengths nor raggedness.  Chunks of 48 groups and more of up to
+// 1024 (eight rows) or 2048 (sixteen) take four waves: us for 1024 of 64 groups, eight
+// rows, 174 / 106 / 125 where all are equally long, 155 / 89 / 61 where they are not (32
+// sequences of 256 to 16383 tokens); ahead of one wave in both.  The number of chunks is
+// that of the grid, from the width of the tables; where shorter sequences leave some of
+// them empty, fewer waves are taken than would be best (64 sequences of 2000 tokens,
+// 32/8 heads, 53 us in tables of 512 groups, 31 in their own).
 static int decode_waves(const DecodeArgs& a) {
-  const long units = (long)a.B * a.Hkv * a.nsplit;
-  const int len = ceil_div(a.max_groups, a.nsplit);  // groups of the longest chunk, or one more
-  if (units <= 256 && len >= 8) return 8;
-  if (units <= 512 && len >= 3) return 4;
+  const long units = (long)a.B * a.Hkv * a.nsplit, buf = a.tk ? (long)a.B * a.Hkv : 0;
+  int len = ceil_div(a.max_groups, a.nsplit);  // groups of the longest chunk
+  if (buf && a.nsplit == 1 && len > 1) --len;  // the table's last is not full yet
+  const bool some = len >= 2 || a.nsplit == 1;
+  const long wgs = units + (len >= 16 ? 0 : len >= 12 ? buf / 2 : buf);
+  if (units <= 256 && ((len >= 6 && units + buf <= (len >= 8 ? 384 : 256)) ||
+                       len >= (a.G <= 8 ? 16 : 32)))
+    return 8;
+  if (wgs <= (a.G <= 8 ? 768 : 512) && len >= (buf || wgs <= 512 ? 3 : 8)) return 4;
+  if (buf && len >= 6 && len < 16) {
+    // past what is resident, by a margin: the buffer's work-groups are the shorter ones
+    const int most = a.G > 8 ? 512 : a.G <= 2 ? 1024 : len < 8 ? 896 : a.G <= 4 ? 1024 : 1152;
+    if (wgs <= most) return 4;
+  }
   if (a.G <= 4) {
-    if (units <= 768 && len >= 8) return 4;
-    return units <= 1536 && len >= (units <= 512 ? 2 : units <= 1024 ? 4 : 8) ? 2 : 1;
+    if (buf)
+      return some && (wgs <= (len == 1 ? 2048 : 1536) || (units <= 1152 && len >= 8) ||
+                      (units <= 1536 && len >= (a.G <= 2 ? 6 : 12))) ? 2 : 1;
+    return units <= 1536 && len >= (units <= 512 ? 2 : units <= 1024 ? 4 : 6) ? 2 : 1;
   }
-  if (a.G <= 8) {
-    if ((units <= 768 && len >= 8) || (units <= 1024 && len >= 48)) return 4;
-    return len >= (units <= 1024 ? 2 : units <= 1536 ? 4 : units <= 2304 ? 32 : 6) ? 2 : 1;
-  }
+  if (len >= 48 && units <= (a.G <= 8 ? 1024 : 2048)) return 4;
+  if (buf) return some ? 2 : 1;
+  if (a.G <= 8) return len >= (units <= 1536 ? 2 : units <= 2304 ? 12 : 4) ? 2 : 1;
   if (units <= 1024) return len >= 2 ? 2 : 1;
-  return units > 1536 && units <= 2560 && len >= 16 ? 4 : 1;
+  return units > 1536 && units <= 2560 && len >= 12 ? 4 : 1;
 }
 
 hipError_t launch_attn_decode(const DecodeArgs& a, hipStream_t stream) {

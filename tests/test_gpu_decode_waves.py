@@ -4,9 +4,10 @@ groups of a chunk, and the result is that of one wave, bit for bit.
 The number of waves follows the number of chunks in the launch and their length,
 so one sequence is decoded alone and repeated 160, 500 and 1000 times (two KV
 heads, one chunk each: 2, 320, 1000 and 2000 chunks); its rows must have the same
-bits each time, and the lone one is checked against the CPU oracle.  Of 9 groups
-that is eight, four, two and one wave for every number of rows; of 64 with eight
-rows eight, four, four and two, with sixteen eight, four, two and four.
+bits each time, and the lone one is checked against the CPU oracle.  With 7 and 9
+groups that is eight, four, two and one wave for every number of rows; with 31 and
+eight rows eight, four, two and two, with sixteen eight, four, two and four; with 64
+and eight rows eight, four, four and two, with sixteen eight, four, four and four.
 """
 import numpy as np
 import pytest
@@ -44,7 +45,7 @@ def _bits(t):
 # row: twice with one wave, once with two); the lengths past which long chunks take
 # other numbers of waves
 CASES = [(G, ng) for G in (1, 2, 4, 8, 16) for ng in (1, 9, 31)] + [
-    (3, 16), (5, 22), (2, 515), (1, 130), (8, 64), (16, 64)]
+    (3, 16), (5, 22), (2, 515), (1, 130), (8, 7), (8, 64), (16, 64)]
 
 
 @pytest.mark.parametrize("G,ng", CASES)
@@ -107,6 +108,39 @@ def test_decode_waves_trace_the_same_integers(ta, dev, G):
             assert np.any(t["pvacc"])
             for name in t:
                 assert np.array_equal(t[name], want[name]), (B, name)
+
+
+@pytest.mark.parametrize("G,ng,N", [(1, 8, 23), (4, 14, 64), (8, 6, 1), (16, 31, 40)])
+def test_decode_waves_with_a_buffer(ta, dev, G, ng, N):
+    """N rows in the int8 buffer, whose work-groups count for the number of waves:
+    1, 160, 300, 500 and 1000 times the same sequence give the bits of one."""
+    print(f"decode waves with a buffer G={G} ng={ng} N={N}", flush=True)
+    Hkv, bits, n = 2, [4, 2], 64 * ng + N % 64
+    k, v = _rand((1, Hkv, n, 128), 110 + G), _rand((1, Hkv, n, 128), 120 + G)
+    q = _rand((1, G * Hkv, 128), 130 + G).to(dev)
+    width = ng + (N % 64 > 0)
+    cache = ta.PagedKVCache(4 * width, width, bits, dev)
+    bt = torch.arange(4 * width, dtype=torch.int32, device=dev)[None]
+    gt = torch.arange(width, dtype=torch.int32, device=dev)[None]
+    res = ta.turbo_quantize_kv(k.to(dev), v.to(dev), cache, bt, gt)
+    one = ta.KVTail(1, Hkv, dev)
+    ta.turbo_tail_init(k.to(dev), v.to(dev), res[2], res[3], one)
+    want = None
+    for B in (1, 160, 300, 500, 1000):
+        tail = ta.KVTail(B, Hkv, dev)
+        tail.k.copy_(one.k.expand_as(tail.k))
+        tail.v.copy_(one.v.expand_as(tail.v))
+        tail.scale.copy_(one.scale.expand_as(tail.scale))
+        sl = torch.full((B,), n, dtype=torch.int32, device=dev)
+        got = ()
+        for split in (1000, 3):
+            got += tuple(ta.turbo_attn_decode(q.repeat(B, 1, 1), cache, sl, bt.repeat(B, 1),
+                                              gt.repeat(B, 1), SM, split, return_lse=True,
+                                              tail=tail))
+        torch.cuda.synchronize()
+        want = got if want is None else want
+        for g, w in zip(got, want):
+            assert torch.equal(_bits(g), _bits(w).expand(B, *w.shape[1:])), B
 
 
 @pytest.mark.parametrize("G,B", [(1, 3), (4, 21), (8, 9)])
