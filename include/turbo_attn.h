@@ -525,13 +525,14 @@ int turbo_decode_default_split(int ng);
 
 /* A chunk length fitted to the occupancy of a decode batch of B sequences,
  * Hq query and Hkv KV heads and max_groups_per_seq (to be passed explicitly
- * as kv_split_groups).  The decode kernel keeps three waves per SIMD resident
- * when Hq / Hkv <= 8 and two otherwise (3072 or 2048 on 256 CUs); the
- * fewest chunks n whose B * Hkv * n waves fill at least two thirds of those
+ * as kv_split_groups).  Chunks are counted as one wave each, with three waves
+ * per SIMD when Hq / Hkv <= 8 and two otherwise (3072 or 2048 on 256 CUs); the
+ * fewest chunks n for which B * Hkv * n fills at least two thirds of those
  * slots are chosen, with chunk length ceil(max_groups_per_seq / n) (the
  * whole sequence when B * Hkv already fills them), but never fewer than two
  * groups per chunk.  Since the chunked result merges SAS-weighted
- * partial states, the output then depends on the batch shape.
+ * partial states, the output then depends on the batch shape.  (How many waves
+ * a launch gives to a chunk does not change the output.)
  * Returns 1 for arguments < 1. */
 int turbo_decode_auto_split(int B, int Hq, int Hkv, int max_groups_per_seq);
 

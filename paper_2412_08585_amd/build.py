@@ -21,8 +21,9 @@ COMMON = [
     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc"),
 ]
 # Translation units and their extra flags.  The attention kernels keep MFMA
-# results in VGPRs (no AGPR round trips before the VALU reads them); the
-# projection keeps its 256 accumulators per lane in the AGPR file.
+# results in VGPRs (no AGPR round trips before the VALU reads them).  The
+# projection is built without that form: its 128 or 64 accumulators per lane
+# fit the VGPRs beside the operands, and the compiler uses no AGPRs.
 UNITS = [
     (os.path.join(HERE, "csrc", "turbo_api.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form"]),
     (os.path.join(HERE, "csrc", "qkv_project.hip"), []),

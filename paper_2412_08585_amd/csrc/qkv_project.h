@@ -1,6 +1,6 @@
 // Arguments and launcher of the fused QKV projection (qkv_project.hip, a
-// translation unit of its own: its accumulators live in the AGPR file, which
-// the attention kernels are built not to use).
+// translation unit of its own, built without the VGPR-only MFMA form that the
+// attention kernels are built with).
 #pragma once
 
 #include <hip/hip_runtime.h>

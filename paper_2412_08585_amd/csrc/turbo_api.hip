@@ -343,15 +343,18 @@ int turbo_decode_default_split(int ng) { return turbo::decode_default_split(ng);
 
 int turbo_decode_auto_split(int B, int Hq, int Hkv, int max_groups_per_seq) {
   if (B < 1 || Hq < 1 || Hkv < 1 || max_groups_per_seq < 1) return 1;
-  // One wave per (sequence, KV head, chunk).  The decode kernel holds three
-  // waves per SIMD when a KV head has at most 8 query heads and two
-  // otherwise: 3072 or 2048 resident waves on the 256 CUs of gfx950.  A
-  // wave's run time is set by its per-group latency chain, and the chunks of
-  // a sequence are merged afterwards, so take the fewest chunks whose waves
-  // fill at least two thirds of the resident slots (one chunk when the
-  // sequences alone do), with the groups spread evenly over them.  A chunk
-  // holds at least two groups: below that the fixed cost of a wave (query
+  // Counted at one wave per (sequence, KV head, chunk), the form that launches of
+  // many chunks take, and at three waves per SIMD when a KV head has at most 8
+  // query heads, two otherwise: 3072 or 2048 on the 256 CUs of gfx950 (with 8 and
+  // 16 rows LDS holds 2304 and 1536 of them).  A chunk's run time is set by its
+  // per-group latency chain, and the chunks of a sequence are merged afterwards,
+  // so take the fewest chunks that fill at least two thirds of these slots (one
+  // chunk when the sequences alone do), with the groups spread evenly over them.
+  // A chunk holds at least two groups: below that the fixed cost of a wave (query
   // quantization, state write) and of the merge outweigh the parallelism.
+  // Where fewer chunks leave slots empty, the launch gives each several waves
+  // (decode_waves).  Those change no bit of the result, the chunk length does:
+  // so this rule does not follow them.
   const long slots = 1024L * ((Hq / Hkv) <= 8 ? 3 : 2);
   const long want = (2 * slots + 2) / 3;
   const long units = (long)B * Hkv, G = max_groups_per_seq;
